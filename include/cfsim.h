@@ -327,23 +327,23 @@ cf_status cf_model_time_kernels(cf_model *m, void *stream, const float *q, const
 int32_t cf_mlp_nparam(void);
 /* y [n][16] = network(feats [n][8]). */
 cf_status cf_mlp_forward(void *stream, const float *params, const float *feats, int32_t n, float *out);
-/* Floats of scratch that cf_mlp_gradient needs for n contacts. */
+/* Floats of scratch that cf_mlp_gradient asks for with n contacts (at least
+ * what its partial sums take). */
 int64_t cf_mlp_work_floats(int32_t n);
 /* Gradient of the mean squared error over the n contacts and the first nout
  * outputs, L = sum (y - targets)^2 / (n nout), targets [n][16]: grad
  * [nparam] (zero for mean and std) and *loss (device scalar, may be NULL).
- * Deterministic: per-wave partial sums in `work`, added in a fixed order. */
+ * Deterministic: partial sums per workgroup in `work`, added in a fixed order. */
 cf_status cf_mlp_gradient(void *stream, const float *params, const float *feats, const float *targets,
                           int32_t n, int32_t nout, float *work, int64_t work_floats, float *grad, float *loss);
 /* cf_mlp_gradient for callers that cannot allocate device memory (code under
  * HIP graph capture, serving or training loops that forbid hipMalloc): the
- * same kernels and the same per-wave partition, so the same grad and loss bit
- * for bit, with the partial sums in a fixed static device array instead of a
- * caller workspace.  Allocates nothing, ever: the array holds the partials of
- * the largest grid the gradient launches (2048 waves x (nparam + 1) floats,
- * 47.5 MB), every GPU the library runs on keeps its own copy until the process
- * ends, and any n >= 1 fits (an n whose partials would not fit is rejected
- * with CF_E_INVALID_ARG).  The first call on a device looks up that device's
+ * same kernels and the same partition, so the same grad and loss bit for bit,
+ * with the partial sums in a fixed static device array instead of a caller
+ * workspace.  Allocates nothing, ever: the array holds the partials of the
+ * largest grid the gradient launches (256 workgroups x 6400 floats, 6.6 MB),
+ * every GPU the library runs on keeps its own copy until the process ends, and
+ * any n >= 1 fits.  The first call on a device looks up that device's
  * copy (CF_E_DEVICE if the lookup fails).  Nothing in the array needs to start
  * at zero; calls that overlap on one GPU share it and race, so serialise
  * them (one stream, or events).  Arguments as for cf_mlp_gradient. */
