@@ -241,11 +241,11 @@ cf_status cf_model_create(const cf_model_desc *d, cf_model **out) {
       if (st.nd > cf::kMaxSubDof) return set_err(CF_E_UNSUPPORTED, "articulated subtree with more than 32 dofs");
       st.lofs = art_floats;
       art_floats += st.nd * st.nd + 9 * st.nd;
-      st.bofs = artb_floats;
-      artb_floats += cf::art_backward_floats(st.nd, st.nb);
       st.small = st.nb <= cf::kSmallSub ? 1 : 0;
       for (int k = b; k < e; ++k)
         if (d->body_jnt[k] == CF_JNT_FREE) st.small = 0;
+      st.bofs = artb_floats;
+      artb_floats += cf::art_backward_floats(st.nd, st.nb, st.small != 0);
       if (st.small) {
         int anc[cf::kSmallSub] = {};
         for (int k = 0; k < st.nb; ++k) {

@@ -165,8 +165,9 @@ size_t mlp_image_bytes();
 hipError_t launch_mlp_pack(const float *params, void *img, hipStream_t s);
 
 size_t backward_lds_bytes(int nq, int nv, int nb, int ng, int block, int nsub, int art_floats, int artb_floats);
-// Floats of the reverse-pass work block of a subtree with nd dofs and nbs bodies.
-int art_backward_floats(int nd, int nbs);
+// Floats of the reverse-pass work block of a subtree with nd dofs and nbs
+// bodies (small: SubTree::small).
+int art_backward_floats(int nd, int nbs, bool small);
 hipError_t launch_backward(const BackwardArgs &a, int nworld, int block, size_t lds, hipStream_t s);
 
 size_t collide_lds_bytes(int nq, int nb, int ng, int norient, int nsub, int nsph);

@@ -3552,11 +3552,17 @@ size_t backward_lds_bytes(int nq, int nv, int nb, int ng, int block, int nsub, i
          sizeof(float4) * (7 * (size_t)nb + 8 * (size_t)block) + sizeof(float) * (size_t)pad4(artb_floats);
 }
 
-// Reverse-pass work block of a subtree (floats): theta bar, v_s bar, y, w,
+// Reverse-pass work block of a small subtree of n bodies (floats): M bar +
+// M bar^T [n n], J bar [n][n][6] (body, dof, linear and angular), then per dof
+// y, c bar, theta bar, theta-dot bar, tau bar.
+__host__ __device__ inline int small_rev_floats(int n) { return 7 * n * n + 5 * n; }
+
+// Reverse-pass work block of any other subtree (floats): theta bar, v_s bar, y, w,
 // tau bar, theta-dot bar, c bar, u [nd each]; M bar [nd nd]; J bar [nbs][6][nd];
 // a free root's direct quaternion adjoint [4]; dual joint values and rates
 // [2 nd], dual root pose [12] and the dual workspace of subtree_phi.
-int art_backward_floats(int nd, int nbs) {
+int art_backward_floats(int nd, int nbs, bool small) {
+  if (small) return small_rev_floats(nbs);
   return nd * nd + 8 * nd + 6 * nd * nbs + 4 + 2 * (2 * nd + 12 + artadj::phi_work(nbs, nd));
 }
 
@@ -3778,6 +3784,284 @@ __device__ void art_rev_predict(const SubTree S, const BodyC *B, const float4 *b
   }
 }
 
+// ---- small subtrees in the reverse pass: lane k of a quad for body and dof k
+// (as art_predict_small), then one lane per body and joint direction for the
+// gradient of Phi (cf_artadj.h).
+struct SmallRev {
+  float *S, *J, *y, *cb, *thb, *thdb, *tb;
+};
+__device__ inline SmallRev small_rev_block(float *bw, int n) {
+  SmallRev r;
+  r.S = bw; r.J = r.S + n * n; r.y = r.J + 6 * n * n; r.cb = r.y + n; r.thb = r.cb + n; r.thdb = r.thb + n;
+  r.tb = r.thdb + n;
+  return r;
+}
+
+// x <- M^-1 x from the Cholesky factor (rows of L, reciprocal diagonal).
+__device__ inline void small_solve(const float (&L)[kSmallSub][kSmallSub], const float (&dinv)[kSmallSub],
+                                   float (&x)[kSmallSub]) {
+#pragma unroll
+  for (int i = 0; i < kSmallSub; ++i) {
+#pragma unroll
+    for (int q = 0; q < i; ++q) x[i] -= L[i][q] * x[q];
+    x[i] *= dinv[i];
+  }
+#pragma unroll
+  for (int i = kSmallSub - 1; i >= 0; --i) {
+#pragma unroll
+    for (int q = i + 1; q < kSmallSub; ++q) x[i] -= L[q][i] * x[q];
+    x[i] *= dinv[i];
+  }
+}
+__device__ inline void small_factor(const float *blk, int n, float (&L)[kSmallSub][kSmallSub],
+                                    float (&dinv)[kSmallSub]) {
+#pragma unroll
+  for (int i = 0; i < kSmallSub; ++i) {
+#pragma unroll
+    for (int j = 0; j < kSmallSub; ++j) L[i][j] = (i < n && j <= i) ? blk[i * n + j] : 0.f;
+    dinv[i] = i < n ? 1.0f / L[i][i] : 0.f;
+  }
+}
+
+// Jacobian columns of body b0 + k's COM (zero off its chain).
+__device__ inline void small_cols(const SubTree S, const SmallChain &C, int k, const float4 *bC, const float4 *bO,
+                                  const float4 *bAx, V3 (&lin)[kSmallSub], V3 (&ang)[kSmallSub]) {
+  const int anc = chain_anc(C, k);
+  const float4 c4 = bC[S.b0 + (k < C.n ? k : 0)];
+  const V3 cb = v3(c4.x, c4.y, c4.z), zero = v3(0.f, 0.f, 0.f);
+#pragma unroll
+  for (int j = 0; j < kSmallSub; ++j) {
+    lin[j] = ang[j] = zero;
+    if (!((anc >> j) & 1)) continue;
+    const float4 o4 = bO[S.b0 + j], a4 = bAx[S.b0 + j];
+    const V3 aj = v3(a4.x, a4.y, a4.z);
+    if (C.jnt[j] == kHinge) {
+      lin[j] = cross(aj, cb - v3(o4.x, o4.y, o4.z));
+      ang[j] = aj;
+    } else {
+      lin[j] = aj;
+    }
+  }
+}
+
+// art_rev_correct of a small subtree: y = M^-1 (v+ bar) in every lane, lane
+// k's body wrench adjoint J_k y; gqo, gvo: the world's output adjoints or null.
+__device__ void small_rev_correct(const SubTree S, int k, const float4 *bC, const float4 *bO, const float4 *bAx,
+                                  const float *blk, float *bw, const float *gqo, const float *gvo, float4 *bFb,
+                                  float4 *bTb, float4 *bQb, float4 *acc, int nb, float h) {
+  constexpr int N = kSmallSub;
+  const SmallChain C = small_chain(S);
+  const int n = C.n;
+  float L[N][N], dinv[N], y[N];
+  small_factor(blk, n, L, dinv);
+#pragma unroll
+  for (int j = 0; j < N; ++j)
+    y[j] = j < n ? (gvo ? gvo[C.dadr[j]] : 0.f) + h * (gqo ? gqo[C.qadr[j]] : 0.f) : 0.f;
+  small_solve(L, dinv, y);
+  if (k >= n) return;
+  V3 lin[N], ang[N], f = v3(0.f, 0.f, 0.f), t = f;
+  small_cols(S, C, k, bC, bO, bAx, lin, ang);
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    f = f + y[j] * lin[j];
+    t = t + y[j] * ang[j];
+  }
+  const int b = S.b0 + k;
+  const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+  small_rev_block(bw, n).y[k] = pick(y, k);
+  bFb[b] = make_float4(f.x, f.y, f.z, 0.f);
+  bTb[b] = make_float4(t.x, t.y, t.z, 0.f);
+  bQb[b] = z;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) acc[i * nb + b] = z;
+}
+
+// art_rev_predict of a small subtree up to the gradient of Phi: lane k adds
+// body k's terms, quad sums give every lane the joint sums, and the quad
+// leaves M bar + M bar^T, c bar, its J bar and the joint adjoints in the block.
+__device__ void small_rev_predict(const SubTree S, int k, const float4 *bC, const float4 *bO, const float4 *bAx,
+                                  const float4 *accF, const float4 *accT, const float *blk, float *bw,
+                                  const float4 *acc, int nb, const float *v0, const float *gqo, const float *gvo,
+                                  const float4 *act, const Params &P) {
+  constexpr int N = kSmallSub;
+  const SmallChain C = small_chain(S);
+  const int n = C.n, b = S.b0 + (k < n ? k : 0);
+  const bool own = k < n;
+  const SmallRev R = small_rev_block(bw, n);
+  float L[N][N], dinv[N], y[N], z[N], vs[N], v[N], thb[N], vsb[N];
+  small_factor(blk, n, L, dinv);
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    const bool in = j < n;
+    y[j] = in ? R.y[j] : 0.f;
+    z[j] = in ? blk[n * n + j] : 0.f;
+    vs[j] = in ? blk[n * n + n + j] : 0.f;
+    v[j] = in ? v0[C.dadr[j]] : 0.f;
+    thb[j] = in && gqo ? gqo[C.qadr[j]] : 0.f;
+    vsb[j] = (in && gvo ? gvo[C.dadr[j]] : 0.f) + P.h * thb[j];
+  }
+  V3 lin[N], ang[N];
+  small_cols(S, C, own ? k : N, bC, bO, bAx, lin, ang);
+  const float4 A0 = acc[b], A1 = acc[nb + b], A2 = acc[2 * nb + b], A3 = acc[3 * nb + b], F = accF[b], T = accT[b];
+  const V3 xb = v3(A0.x, A0.y, A0.z), pb = v3(A0.w, A1.x, A1.y);
+  const V3 vb = v3(A1.z, A1.w, A2.x), wb = v3(A2.y, A2.z, A2.w);
+  const float trb = own ? A3.x : 0.f;
+  // u_r = M^-1 (row r of the COM Jacobian), the trace's derivative
+  float u0[N], u1[N], u2[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    u0[j] = lin[j].x; u1[j] = lin[j].y; u2[j] = lin[j].z;
+  }
+  small_solve(L, dinv, u0);
+  small_solve(L, dinv, u1);
+  small_solve(L, dinv, u2);
+  const int anc = own ? chain_anc(C, k) : 0;
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    thb[j] += quad_sum(dot(lin[j], xb) + dot(ang[j], pb));
+    vsb[j] += quad_sum(dot(lin[j], vb) + dot(ang[j], wb));
+    if (own && j < n) {
+      const bool on = (anc >> j) & 1;
+      const float t2 = on ? 2.f * trb : 0.f, yj = on ? y[j] : 0.f, vj = on ? vs[j] : 0.f;
+      float *J = R.J + 6 * (k * n + j);
+      J[0] = F.x * yj + vb.x * vj + t2 * u0[j];
+      J[1] = F.y * yj + vb.y * vj + t2 * u1[j];
+      J[2] = F.z * yj + vb.z * vj + t2 * u2[j];
+      J[3] = T.x * yj + wb.x * vj;
+      J[4] = T.y * yj + wb.y * vj;
+      J[5] = T.z * yj + wb.z * vj;
+    }
+  }
+  // v_s = thd + h s, s = M^-1 (tau - c): w = h M^-1 (v_s bar)
+  float w[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) w[j] = P.h * vsb[j];
+  small_solve(L, dinv, w);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const float si = (vs[i] - v[i]) / P.h;
+#pragma unroll
+    for (int j = 0; j <= i; ++j) {
+      const float sj = (vs[j] - v[j]) / P.h;
+      const float tr = quad_sum(trb * (u0[i] * u0[j] + u1[i] * u1[j] + u2[i] * u2[j]));
+      const float m = -(y[i] * z[j] + y[j] * z[i]) - (w[i] * sj + w[j] * si) - 2.f * tr;
+      if (k == 0 && i < n) R.S[i * n + j] = R.S[j * n + i] = m;
+    }
+  }
+  if (own) {
+    const float wk = pick(w, k);
+    float tk = pick(thb, k), dk = pick(vsb, k), tau = wk;
+    if (act) {  // tau = kp (u - theta) - kd theta-dot for an actuated dof
+      const float4 c = act[chain_dadr(C, k)];
+      if (__float_as_int(c.z) >= 0) {
+        tk -= c.x * wk;
+        dk -= c.y * wk;
+        tau *= c.x;
+      }
+    }
+    R.cb[k] = -wk;
+    R.thb[k] = tk;
+    R.thdb[k] = dk;
+    R.tb[k] = tau;
+  }
+}
+
+// Vector with one directional derivative.
+struct D3 {
+  V3 v, d;
+};
+__device__ inline D3 operator+(D3 a, D3 b) { return {a.v + b.v, a.d + b.d}; }
+__device__ inline D3 operator-(D3 a, D3 b) { return {a.v - b.v, a.d - b.d}; }
+__device__ inline D3 cross(D3 a, D3 b) { return {cross(a.v, b.v), cross(a.d, b.v) + cross(a.v, b.d)}; }
+__device__ inline D3 scale(float s, float sd, D3 a) { return {s * a.v, sd * a.v + s * a.d}; }
+
+// Body k's share of the derivative of Phi (cf_artadj.h) of a small subtree
+// along joint angle `dir` (dir < kSmallSub) or joint rate dir - kSmallSub.
+// Turning joint x moves everything above it rigidly, so the derivatives of
+// origins, axes, COM and inertia are a_x x (.) (a_x for a slide) of the frames
+// already in LDS, and no kinematics are differentiated.  The frames' float64
+// kinematics (narrow phase) give the values.
+__device__ float small_phi_dir(const SubTree S, const SmallChain &C, int k, int dir, const float4 *bC, const float4 *bO,
+                               const float4 *bAx, const float4 *bR, float4 mi, const float *bw, const float *v0,
+                               const Params &P) {
+  constexpr int N = kSmallSub;
+  const int n = C.n, anc = chain_anc(C, k);
+  const int x = dir < N ? dir : -1, rate = dir < N ? -1 : dir - N;
+  const SmallRev R = small_rev_block(const_cast<float *>(bw), n);
+  const V3 zero = v3(0.f, 0.f, 0.f);
+  auto xyz = [](float4 f) { return v3(f.x, f.y, f.z); };
+  const V3 ax = x >= 0 ? xyz(bAx[S.b0 + x]) : zero, ox = x >= 0 ? xyz(bO[S.b0 + x]) : zero;
+  const bool hinge = x >= 0 && ((C.chain >> (16 + x)) & 1);
+  // joint x moves point p of body j: j has x on its chain
+  auto moved = [&](int j) { return x >= 0 && ((chain_anc(C, j) >> x) & 1); };
+  auto point = [&](V3 p, bool m) -> D3 { return {p, m ? (hinge ? cross(ax, p - ox) : ax) : zero}; };
+  auto axis = [&](V3 a, bool m) -> D3 { return {a, m && hinge ? cross(ax, a) : zero}; };
+  const D3 c = point(xyz(bC[S.b0 + k]), moved(k));
+  D3 lin[N], ang[N], om = {zero, zero}, al = om, acc = om, po = om;
+  D3 U = om, V = om;  // sum of c bar_j times the columns
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    lin[j] = ang[j] = {zero, zero};
+    if (!((anc >> j) & 1)) continue;
+    const bool m = moved(j), hj = C.jnt[j] == kHinge;
+    const D3 o = point(xyz(bO[S.b0 + j]), m), a = axis(xyz(bAx[S.b0 + j]), m);
+    // velocity-product acceleration along the chain (zero at the first joint)
+    const D3 d = o - po;
+    acc = acc + cross(al, d) + cross(om, cross(om, d));
+    po = o;
+    const D3 ra = scale(v0[C.dadr[j]], rate == j ? 1.f : 0.f, a);
+    if (hj) {
+      lin[j] = cross(a, c - o);
+      ang[j] = a;
+      al = al + cross(om, ra);
+      om = om + ra;
+    } else {
+      lin[j] = a;
+      acc = acc + scale(2.f, 0.f, cross(om, ra));
+    }
+    U = U + scale(R.cb[j], 0.f, lin[j]);
+    V = V + scale(R.cb[j], 0.f, ang[j]);
+  }
+  const D3 r = c - po;
+  acc = acc + cross(al, r) + cross(om, cross(om, r));
+  // world inertia R diag(I) R^T applied to a vector, and its change with the turn
+  const V3 r0 = xyz(bR[3 * (S.b0 + k)]), r1 = xyz(bR[3 * (S.b0 + k) + 1]), r2 = xyz(bR[3 * (S.b0 + k) + 2]);
+  auto inertia = [&](V3 u) {
+    const float b0 = mi.y * (r0.x * u.x + r1.x * u.y + r2.x * u.z), b1 = mi.z * (r0.y * u.x + r1.y * u.y + r2.y * u.z),
+                b2 = mi.w * (r0.z * u.x + r1.z * u.y + r2.z * u.z);
+    return v3(r0.x * b0 + r0.y * b1 + r0.z * b2, r1.x * b0 + r1.y * b1 + r1.z * b2, r2.x * b0 + r2.y * b1 + r2.z * b2);
+  };
+  const V3 wx = moved(k) && hinge ? ax : zero;  // the body's rotation increment
+  auto inertia_d = [&](D3 u) -> D3 {             // (I u)' = w x I u + I (u' - w x u)
+    const V3 Iu = inertia(u.v);
+    return {Iu, cross(wx, Iu) + inertia(u.d - cross(wx, u.v))};
+  };
+  const V3 g = v3(P.gx, P.gy, P.gz);
+  const V3 Fl = mi.x * (acc.v - g), Fld = mi.x * acc.d;
+  const D3 Fa = inertia_d(al) + cross(om, inertia_d(om));
+  float phi = dot(U.d, Fl) + dot(U.v, Fld) + dot(V.d, Fa.v) + dot(V.v, Fa.d);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (!((anc >> i) & 1)) continue;
+    V3 l = zero, t = zero;  // rows of (M bar + M bar^T) against the columns
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      if (!((anc >> j) & 1)) continue;
+      const float m = R.S[i * n + j];
+      l = l + m * lin[j].v;
+      t = t + m * ang[j].v;
+    }
+    const V3 It = inertia(t);
+    // <M bar, J^T diag(m, I) J>: the columns' change, then the inertia's,
+    // I' t = w x (I t) - I (w x t), half of it per row of the symmetric form
+    phi += mi.x * dot(lin[i].d, l) + dot(ang[i].d, It);
+    phi += 0.5f * (dot(ang[i].v, cross(wx, It)) - dot(ang[i].v, inertia(cross(wx, t))));
+    const float *J = R.J + 6 * (k * n + i);
+    phi += dot(lin[i].d, v3(J[0], J[1], J[2])) + dot(ang[i].d, v3(J[3], J[4], J[5]));
+  }
+  return phi;
+}
+
 // Reverse of one step of world w: the forward step is recomputed in LDS
 // (same code as the resolution kernel, so the same contact set, facet
 // activity and branches), then the adjoints run backwards through
@@ -3846,12 +4130,19 @@ __global__ __launch_bounds__(BS) void backward_kernel(BackwardArgs b) {
   };
 
   // ---- reverse of integration and correction, per free body and per subtree
+  // (lanes 4 si .. 4 si + 3 take subtree si: a quad for a small one, its first
+  // lane for any other)
+  const float *gqo = b.gq_out ? b.gq_out + (size_t)w * nq : nullptr;
+  const float *gvo = b.gv_out ? b.gv_out + (size_t)w * nv : nullptr;
   if (ART)
-  for (int si = tid; si < a.nsub; si += BS) {
-    const SubTree S = a.sub[si];
-    art_rev_correct(S, a.body, RR.bC, RR.bO, RR.bAx, RR.accF, RR.accT, RR.art + S.lofs, artb + S.bofs, sq0, sv,
-                    b.gq_out ? b.gq_out + (size_t)w * nq : nullptr, b.gv_out ? b.gv_out + (size_t)w * nv : nullptr,
-                    bFb, bTb, bQb, acc, nb, P.h);
+  for (int t = tid; t < 4 * a.nsub; t += BS) {
+    const SubTree S = a.sub[t >> 2];
+    if (S.small)
+      small_rev_correct(S, t & 3, RR.bC, RR.bO, RR.bAx, RR.art + S.lofs, artb + S.bofs, gqo, gvo, bFb, bTb, bQb, acc,
+                        nb, P.h);
+    else if ((t & 3) == 0)
+      art_rev_correct(S, a.body, RR.bC, RR.bO, RR.bAx, RR.accF, RR.accT, RR.art + S.lofs, artb + S.bofs, sq0, sv, gqo,
+                      gvo, bFb, bTb, bQb, acc, nb, P.h);
   }
   for (int bi = tid; bi < nb; bi += BS) {
     const BodyC bc = a.body[bi];
@@ -4040,11 +4331,39 @@ __global__ __launch_bounds__(BS) void backward_kernel(BackwardArgs b) {
 
   // ---- reverse of the smooth prediction, per free body and per subtree;
   // adjoint rows staged in LDS
-  if (ART)
-  for (int si = tid; si < a.nsub; si += BS) {
-    const SubTree S = a.sub[si];
-    art_rev_predict(S, a.body, a.bmi + (size_t)w * nb, RR.bC, RR.bO, RR.bAx, RR.art + S.lofs, artb + S.bofs, acc, nb,
-                    sq0, vw, a.act, P, sq, sv, st);
+  if (ART) {
+    for (int t = tid; t < 4 * a.nsub; t += BS) {
+      const SubTree S = a.sub[t >> 2];
+      if (S.small)
+        small_rev_predict(S, t & 3, RR.bC, RR.bO, RR.bAx, RR.accF, RR.accT, RR.art + S.lofs, artb + S.bofs, acc, nb,
+                          vw, gqo, gvo, a.act, P);
+      else if ((t & 3) == 0)
+        art_rev_predict(S, a.body, a.bmi + (size_t)w * nb, RR.bC, RR.bO, RR.bAx, RR.art + S.lofs, artb + S.bofs, acc,
+                        nb, sq0, vw, a.act, P, sq, sv, st);
+    }
+    __syncthreads();
+    // small subtrees: thirty-two lanes each, a quad (one lane per body) for
+    // each of up to eight joint directions, which finishes its joint's adjoint
+    for (int t = tid; t < 8 * kSmallSub * a.nsub; t += BS) {
+      const SubTree S = a.sub[t / (8 * kSmallSub)];
+      const int dir = (t >> 2) & 7, k = t & 3, j = dir & (kSmallSub - 1);
+      if (!S.small || j >= S.nb) continue;
+      const SmallChain C = small_chain(S);
+      float *bw = artb + S.bofs;
+      float d = 0.f;
+      if (k < S.nb)
+        d = small_phi_dir(S, C, k, dir, RR.bC, RR.bO, RR.bAx, RR.bR, a.bmi[(size_t)w * nb + S.b0 + k], bw, vw, P);
+      d = quad_sum(d);
+      if (k == 0) {
+        const SmallRev R = small_rev_block(bw, S.nb);
+        if (dir < kSmallSub) {
+          sq[C.q0 + j] = R.thb[j] + d;
+          st[C.d0 + j] = R.tb[j];
+        } else {
+          sv[C.d0 + j] = R.thdb[j] + d;
+        }
+      }
+    }
   }
   for (int bi = tid; bi < nb; bi += BS) {
     const BodyC bc = a.body[bi];
