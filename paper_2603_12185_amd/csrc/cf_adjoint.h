@@ -148,15 +148,30 @@ struct BodyUpdate {
   T h;
 };
 
+// cos(a/2), s(a) = sin(a/2)/a and s'(a)/a of a rotation angle a: below a = 1/2
+// by their series (first omitted terms below 1e-11 relative), without sine,
+// cosine or a division; s' cancels in closed form for small angles.
+template <class T>
+CF_HD void half_angle(T a, T &c, T &s, T &ds) {
+  if (a < T(0.5)) {
+    const T x2 = T(0.25) * a * a;
+    c = T(1) - x2 * (T(1) / T(2) - x2 * (T(1) / T(24) - x2 * (T(1) / T(720) - x2 * (T(1) / T(40320) -
+        x2 * (T(1) / T(3628800))))));
+    s = T(0.5) * (T(1) - x2 * (T(1) / T(6) - x2 * (T(1) / T(120) - x2 * (T(1) / T(5040) - x2 * (T(1) / T(362880))))));
+    ds = T(-1) / T(24) + x2 * (T(1) / T(240) - x2 * (T(1) / T(6720) - x2 * (T(1) / T(362880) - x2 * (T(1) / T(31933440)))));
+  } else {
+    const T sn = sin(T(0.5) * a);
+    c = cos(T(0.5) * a);
+    s = sn / a;
+    ds = (T(0.5) * a * c - sn) / (a * a * a);
+  }
+}
+
 template <class T>
 CF_HD void quat_exp(Vec<T> th, T *e) {
-  const T ang = sqrt(dot(th, th));
-  if (ang < T(1e-8)) {
-    e[0] = T(1); e[1] = T(0.5) * th.x; e[2] = T(0.5) * th.y; e[3] = T(0.5) * th.z;
-  } else {
-    const T s = sin(T(0.5) * ang) / ang;
-    e[0] = cos(T(0.5) * ang); e[1] = s * th.x; e[2] = s * th.y; e[3] = s * th.z;
-  }
+  T c, s, ds;
+  half_angle(T(sqrt(dot(th, th))), c, s, ds);
+  e[0] = c; e[1] = s * th.x; e[2] = s * th.y; e[3] = s * th.z;
 }
 
 template <class T>
@@ -195,8 +210,9 @@ CF_HD void update_vjp(const BodyUpdate<T> &B, Vec<T> xpb, const T *qpb, Vec<T> v
   rot_diag_rot(R, e3, Ii);
   const Vec<T> wp = B.ws + sym_mul(Ii, B.Tq);
   const Vec<T> th = B.h * wp;
-  T e[4], qn[4];
-  quat_exp(th, e);
+  T qn[4], c, s, ds;
+  half_angle(T(sqrt(dot(th, th))), c, s, ds);
+  const T e[4] = {c, s * th.x, s * th.y, s * th.z};
   quat_mul(e, B.q, qn);
   const T l = sqrt(qn[0] * qn[0] + qn[1] * qn[1] + qn[2] * qn[2] + qn[3] * qn[3]);
   const T il = T(1) / l;
@@ -217,18 +233,7 @@ CF_HD void update_vjp(const BodyUpdate<T> &B, Vec<T> xpb, const T *qpb, Vec<T> v
   qb[3] += -e[3] * g[0] + e[2] * g[1] - e[1] * g[2] + e[0] * g[3];
   // e = exp(th): e_w = cos(a/2), e_v = s(a) th with s(a) = sin(a/2)/a
   const Vec<T> ev = vec(eb[1], eb[2], eb[3]);
-  Vec<T> thb;
-  const T a = sqrt(dot(th, th));
-  if (a < T(1e-8)) {
-    thb = T(0.5) * ev;
-  } else {
-    const T s = sin(T(0.5) * a) / a;
-    // s'(a) / a, by its series where the closed form cancels
-    const T a2 = a * a;
-    const T ds_a = a < T(0.05) ? T(-1) / T(24) + a2 / T(960)
-                               : (T(0.5) * a * cos(T(0.5) * a) - sin(T(0.5) * a)) / (a2 * a);
-    thb = (-eb[0] * sin(T(0.5) * a) / (T(2) * a) + ds_a * dot(th, ev)) * th + s * ev;
-  }
+  const Vec<T> thb = (T(-0.5) * eb[0] * s + ds * dot(th, ev)) * th + s * ev;
   const Vec<T> wpt = wpb + B.h * thb;
   const Vec<T> vpt = vpb + B.h * xpb;
   xb = xpb;
@@ -254,10 +259,13 @@ CF_HD T impedance_rho(T phi, const Impedance<T> &P, T &drho) {
   const T x = clamped ? T(1) : x0;
   const bool lo = x < P.mid;
   const T u = lo ? x / P.mid : (T(1) - x) / (T(1) - P.mid);
-  const T up = pow(u, P.power);
+  // u^p and u^(p - 1); the default power p = 2 without pow, whose two calls
+  // were a third of a contact's reverse pass
+  const bool square = P.power == T(2);
+  const T up = square ? u * u : pow(u, P.power), up1 = square ? u : pow(u, P.power - T(1));
   const T gam = lo ? P.mid * up : T(1) - (T(1) - P.mid) * up;
   const T r = P.r_min + (P.r_max - P.r_min) * gam;
-  const T dgam = P.power * pow(u, P.power - T(1));  // d gamma / dx on both branches
+  const T dgam = P.power * up1;  // d gamma / dx on both branches
   const T dx = clamped ? T(0) : (phi > T(0) ? T(1) : phi < T(0) ? T(-1) : T(0)) / P.width;
   drho = (P.r_max - P.r_min) * dgam * dx / ((T(1) - r) * (T(1) - r));
   return r / (T(1) - r);
