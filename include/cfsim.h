@@ -196,6 +196,19 @@ cf_status cf_step(cf_model *m, void *stream, const float *q, const float *v, con
 cf_status cf_step_backward(cf_model *m, void *stream, const float *q, const float *v, const float *tau,
                            const float *gq_out, const float *gv_out, float *gq, float *gv, float *gtau);
 
+/* Adjoint of a rollout: the chain of cf_step_backward over its stored
+ * trajectory.  q_traj/v_traj [T+1][nworld][nq|nv] as cf_rollout left them,
+ * tau_seq [T][nworld][nv] or NULL; gq_traj/gv_traj [T+1][...]: the adjoints
+ * of every state (either may be NULL = zero).  Writes gq0 [nworld][nq] and gv0
+ * [nworld][nv], the adjoints of the initial state, and gtau_seq [T][nworld][nv]
+ * (may be NULL).  T >= 1; buffers and, for T > 1, every step's rows 16-byte
+ * aligned; outputs overlap nothing.  Worlds of at most 64 free bodies without
+ * learned gains run all T steps in one kernel launch; other models take T
+ * cf_step_backward calls on the stream.  Allocates nothing. */
+cf_status cf_rollout_backward(cf_model *m, void *stream, int32_t T, const float *q_traj, const float *v_traj,
+                              const float *tau_seq, const float *gq_traj, const float *gv_traj, float *gq0,
+                              float *gv0, float *gtau_seq);
+
 /* T consecutive steps (batched rollouts): q_traj/v_traj [T+1][nworld][nq|nv]
  * receive the initial state (copied from q0/v0 unless they already alias row 0)
  * and every step's result; tau_seq [T][nworld][nv] or NULL; ncon_traj

@@ -3,9 +3,9 @@
 `step(model, q, v, tau)` and `rollout(model, T, q0, v0, tau_seq)` return
 tensors that carry gradients back through the library's hand-written adjoint
 (`cf_step_backward`).  A rollout keeps every step's state (the trajectory it
-returns anyway) as its checkpoint; its backward walks the steps in reverse,
-each call recomputing its step's forward pass on the GPU from the stored
-(q_t, v_t, tau_t).  Gradients are those of the piecewise-smooth step on the
+returns anyway) as its checkpoint; its backward (`cf_rollout_backward`) walks
+the steps in reverse, recomputing each step's forward pass on the GPU from the
+stored (q_t, v_t, tau_t).  Gradients are those of the piecewise-smooth step on the
 piece that contains the forward trajectory (contact sets and facet activity
 held fixed).  Only argument marshalling happens here; all arithmetic runs in
 the HIP library.
@@ -52,22 +52,15 @@ class _Rollout(torch.autograd.Function):
         q_traj, v_traj, tau_seq = ctx.saved_tensors
         model, T = ctx.model, ctx.T
         nw = model.nworld
-        if gq_traj is None:
-            gq_traj = torch.zeros_like(q_traj)
-        if gv_traj is None:
-            gv_traj = torch.zeros_like(v_traj)
-        gq = gq_traj[T].clone()
-        gv = gv_traj[T].clone()
         gtau_seq = torch.empty((T, nw, model.nv), dtype=torch.float32, device=q_traj.device) \
             if ctx.has_tau else None
-        gq_t, gv_t = torch.empty_like(gq), torch.empty_like(gv)
-        scratch_tau = torch.empty_like(gv)
-        for t in range(T - 1, -1, -1):
-            tau_t = tau_seq[t] if ctx.has_tau else None
-            gtau_t = gtau_seq[t] if ctx.has_tau else scratch_tau
-            model.step_backward(q_traj[t], v_traj[t], tau_t, gq, gv, gq=gq_t, gv=gv_t, gtau=gtau_t)
-            gq = gq_t + gq_traj[t]
-            gv = gv_t + gv_traj[t]
+        if T == 0:
+            gq = torch.zeros_like(q_traj[0]) if gq_traj is None else gq_traj[0].clone()
+            gv = torch.zeros_like(v_traj[0]) if gv_traj is None else gv_traj[0].clone()
+            return None, None, gq, gv, gtau_seq
+        gq, gv = model.rollout_backward(T, q_traj, v_traj, tau_seq if ctx.has_tau else None,
+                                        None if gq_traj is None else gq_traj.contiguous(),
+                                        None if gv_traj is None else gv_traj.contiguous(), gtau_seq)
         return None, None, gq, gv, gtau_seq
 
 

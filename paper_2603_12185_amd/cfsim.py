@@ -61,6 +61,7 @@ SIGNATURES = {
     "cf_step": ([C.c_void_p, C.c_void_p, _fp, _fp, _fp, _fp, _fp, C.POINTER(Contacts)], C.c_int32),
     "cf_rollout": ([C.c_void_p, C.c_void_p, C.c_int32, _fp, _fp, _fp, _fp, _fp, _fp, _fp], C.c_int32),
     "cf_step_backward": ([C.c_void_p, C.c_void_p, _fp, _fp, _fp, _fp, _fp, _fp, _fp, _fp], C.c_int32),
+    "cf_rollout_backward": ([C.c_void_p, C.c_void_p, C.c_int32, _fp, _fp, _fp, _fp, _fp, _fp, _fp, _fp], C.c_int32),
     "cf_model_set_launch": ([C.c_void_p, C.c_int32, C.c_int32, C.c_int32], C.c_int32),
     "cf_model_set_impedance": ([C.c_void_p, C.c_int32], C.c_int32),
     "cf_model_set_actuators": ([C.c_void_p, C.POINTER(C.c_float), C.POINTER(C.c_float)], C.c_int32),
@@ -275,6 +276,24 @@ class Model:
                                  _ptr(tau_seq), _ptr(q_traj), _ptr(v_traj), _ptr(ncon_traj),
                                  _ptr(overflow_traj)))
         return q_traj, v_traj
+
+    def rollout_backward(self, T, q_traj, v_traj, tau_seq, gq_traj, gv_traj, gtau_seq=None, stream=None):
+        """Adjoint of rollout(): (gq0, gv0) from the adjoints gq_traj, gv_traj (or
+        None) of every state of the trajectory; gtau_seq [T][nworld][nv], when
+        given, receives those of the step inputs."""
+        import torch
+        for t, rows, cols, name in ((q_traj, T + 1, self.nq, "q_traj"), (v_traj, T + 1, self.nv, "v_traj"),
+                                    (tau_seq, T, self.nv, "tau_seq"), (gq_traj, T + 1, self.nq, "gq_traj"),
+                                    (gv_traj, T + 1, self.nv, "gv_traj"), (gtau_seq, T, self.nv, "gtau_seq")):
+            if t is not None:
+                self._check_state(t, rows * cols, name)
+        gq = torch.empty_like(q_traj[0])
+        gv = torch.empty_like(v_traj[0])
+        s = torch.cuda.current_stream() if stream is None else stream
+        _check(load().cf_rollout_backward(self._h, C.c_void_p(s.cuda_stream), int(T), _ptr(q_traj), _ptr(v_traj),
+                                          _ptr(tau_seq), _ptr(gq_traj), _ptr(gv_traj), _ptr(gq), _ptr(gv),
+                                          _ptr(gtau_seq)))
+        return gq, gv
 
     # ------------------------------------------------------------ launch shape
     def set_learned_impedance(self, net, margin=0.0):

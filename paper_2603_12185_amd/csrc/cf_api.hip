@@ -52,8 +52,11 @@ struct cf_model {
   size_t lds_rollout = 0;
   size_t lds_rollout_free = 0;  // persistent rollout of free bodies (0: not applicable)
   int ncu = 256;                // compute units of the model's device
-  int block_backward = 0;  // 0: the adjoint's LDS does not fit any workgroup size
-  size_t lds_backward = 0;
+  // the adjoint's workgroup without and with learned gains (0: its LDS fits no size)
+  int block_backward[2] = {0, 0};
+  size_t lds_backward[2] = {0, 0};
+  size_t lds_adjoint_free = 0;  // persistent adjoint of free bodies (0: not applicable)
+  int adjoint_con = 0;          // contact records it keeps in LDS (0: in the workspace)
   bool rollout_steps = false;  // autotuner found T cf_step calls faster than the persistent kernel
   float4 *d_bmi = nullptr, *d_gdat = nullptr, *d_gpos = nullptr, *d_gquat = nullptr;
   float *d_gmu = nullptr;  // [nworld][ngeom] tangential friction alone
@@ -436,13 +439,36 @@ cf_status cf_model_create(const cf_model_desc *d, cf_model **out) {
   m->lds_rollout = rollout_lds(m);
   if (m->nsub == 0 && cf::rollout_free_fits(m->nq, nb))
     m->lds_rollout_free = cf::rollout_free_lds_bytes(nb, ng, m->norient, m->nsph);
-  for (int bs : {256, 128, 64}) {
-    const size_t l = cf::backward_lds_bytes(m->nq, m->nv, nb, ng, bs, m->nsub, m->art_floats, m->artb_floats);
-    if (l <= kLdsLimit) { m->block_backward = bs; m->lds_backward = l; break; }
+  if (m->nsub == 0 && nb >= 1 && nb <= 64) {
+    // a world never holds more contacts than slots: up to 128 records (4 KB) stay in LDS
+    const int con = std::min(m->ncon_max, m->nslot);
+    m->adjoint_con = con >= 1 && con <= 128 ? con : 0;
+    m->lds_adjoint_free = cf::adjoint_free_lds_bytes(m->nq, nb, ng, m->norient, m->nsph, m->adjoint_con);
+    if (m->lds_adjoint_free > kLdsLimit) m->lds_adjoint_free = 0;
   }
   if (hipGetDevice(&m->dev) != hipSuccess) { delete m; return set_err(CF_E_DEVICE, "no HIP device"); }
   if (hipDeviceGetAttribute(&m->ncu, hipDeviceAttributeMultiprocessorCount, m->dev) != hipSuccess || m->ncu < 1)
     m->ncu = 256;
+  // The adjoint's workgroup.  A contact takes a lane, so worlds of many bodies
+  // (and contacts) start at 256 threads, subtrees at 128 (a hand's 12 contacts
+  // and four fingers' 128 body-direction lanes), small worlds at 64; halved
+  // while the batch holds more than two waves per SIMD (down to 128 for many
+  // contacts).  Microseconds at 256 / 128 / 64 threads: 64 spheres x 256 worlds
+  // 24 / 30 / 40, x 1024 43 / 34 / 43, x 4096 146 / 116 / 161; 24 spheres x 2048
+  // 47 / 34 / 23; hand x 256 42 / 41 / 44, x 1024 80 / 45 / 49, x 2048 145 / 103 / 56.
+  // With learned gains a contact evaluates the network in its lane: 256 always
+  // (64 spheres x 256 worlds 192 / 716 / 1327).
+  const int fewest = nb > 32 ? 128 : 64;
+  int want = nb > 32 ? 256 : m->nsub > 0 ? 128 : 64;
+  while (want > fewest && (size_t)nw * (want / 64) > (size_t)8 * m->ncu) want /= 2;
+  for (int learned = 0; learned < 2; ++learned)
+    for (int bs : {256, 128, 64}) {
+      const size_t l = cf::backward_lds_bytes(m->nq, m->nv, nb, ng, bs, m->nsub, m->art_floats, m->artb_floats);
+      if (l > kLdsLimit || (!learned && bs > want)) continue;
+      m->block_backward[learned] = bs;
+      m->lds_backward[learned] = l;
+      break;
+    }
 
   // ---- per-world constants (float32); shared arrays get world stride 0
   std::vector<float4> bmi((size_t)nw * nb), gdat(wg), gpos, gquat;
@@ -693,6 +719,44 @@ cf_status cf_step(cf_model *m, void *stream, const float *q, const float *v, con
   return CF_OK;
 }
 
+// Whether the adjoint covers the model.
+static cf_status adjoint_supported(const cf_model *m) {
+  if (m->p.imp_diag && m->nsub > 0)
+    return set_err(CF_E_UNSUPPORTED, "cf_step_backward covers the diagonal impedance on models of free bodies only");
+  if (!m->block_backward[0]) return set_err(CF_E_UNSUPPORTED, "world too large for the adjoint's LDS");
+  return CF_OK;
+}
+
+// Worlds of at most 64 free bodies without learned gains take the persistent
+// one-wave adjoint kernel for a trajectory (one launch for its T steps), and for
+// a single step while the batch is one wave per SIMD and a world's contacts
+// are few: microseconds against the two kernels, 24 spheres x 256 worlds 16 / 19,
+// x 2048 32 / 23; 40 spheres x 256 23 / 22; 64 spheres 32 / 24 (their contacts
+// fill four waves at once); 16 steps of 256 worlds, per step, 16 spheres 9.2 / 20,
+// 64 spheres 27 / 28.
+static bool adjoint_free(const cf_model *m, int T) {
+  if (m->lds_adjoint_free == 0 || m->d_act || m->mlp) return false;
+  return T > 1 || (m->nb <= 32 && m->nw <= 4 * m->ncu);
+}
+
+static cf::BackwardArgs backward_args(const cf_model *m) {
+  cf::BackwardArgs b{};
+  b.s = resolve_args(m);
+  b.s.mlp = m->mlp;  // learned gains: the adjoint recomputes them from the float32 parameters
+  b.gpos = m->d_gpos; b.gpos_ws = m->gpos_ws;
+  b.gquat = m->d_gquat; b.gquat_ws = m->gquat_ws;
+  return b;
+}
+
+static cf::AdjointArgs adjoint_args(const cf_model *m) {
+  cf::AdjointArgs r{};
+  r.c = collide_args(m);
+  r.b = backward_args(m);
+  r.nworld = m->nw;
+  r.con = m->adjoint_con;
+  return r;
+}
+
 cf_status cf_step_backward(cf_model *m, void *stream, const float *q, const float *v, const float *tau,
                            const float *gq_out, const float *gv_out, float *gq, float *gv, float *gtau) {
   if (!m) return set_err(CF_E_INVALID_ARG, "model is NULL");
@@ -713,23 +777,76 @@ cf_status cf_step_backward(cf_model *m, void *stream, const float *q, const floa
       overlap(gtau, sv, q, sq) || overlap(gtau, sv, v, sv) || overlap(gtau, sv, tau, sv) ||
       overlap(gtau, sv, gq_out, sq) || overlap(gtau, sv, gv_out, sv))
     return set_err(CF_E_INVALID_ARG, "gq/gv may alias gq_out/gv_out only exactly; no other overlap");
-  if (m->p.imp_diag && m->nsub > 0)
-    return set_err(CF_E_UNSUPPORTED, "cf_step_backward covers the diagonal impedance on models of free bodies only");
-  if (!m->block_backward) return set_err(CF_E_UNSUPPORTED, "world too large for the adjoint's LDS");
+  if (const cf_status st = adjoint_supported(m); st != CF_OK) return st;
   hipStream_t s = (hipStream_t)stream;
+  if (adjoint_free(m, 1)) {
+    cf::AdjointArgs r = adjoint_args(m);
+    r.q_traj = q; r.v_traj = v; r.tau_seq = tau; r.gq_end = gq_out; r.gv_end = gv_out;
+    r.gq = gq; r.gv = gv; r.gtau = gtau; r.T = 1;
+    const hipError_t e = cf::launch_adjoint_free(r, m->lds_adjoint_free, s);
+    if (e != hipSuccess) return set_err(CF_E_DEVICE, std::string("adjoint launch: ") + hipGetErrorString(e));
+    return CF_OK;
+  }
   cf::CollideArgs ca = collide_args(m);
   ca.q = q;
   hipError_t e = cf::launch_collide(ca, m->nw, m->block_collide, m->lds_collide, s);
   if (e != hipSuccess) return set_err(CF_E_DEVICE, std::string("collide launch: ") + hipGetErrorString(e));
-  cf::BackwardArgs b{};
-  b.s = resolve_args(m);
-  b.s.mlp = m->mlp;  // learned gains: the adjoint recomputes them from the float32 parameters
+  cf::BackwardArgs b = backward_args(m);
   b.s.q = q; b.s.v = v; b.s.tau = tau;
-  b.gpos = m->d_gpos; b.gpos_ws = m->gpos_ws;
-  b.gquat = m->d_gquat; b.gquat_ws = m->gquat_ws;
   b.gq_out = gq_out; b.gv_out = gv_out; b.gq = gq; b.gv = gv; b.gtau = gtau;
-  e = cf::launch_backward(b, m->nw, m->block_backward, m->lds_backward, s);
+  const int l = m->mlp ? 1 : 0;
+  e = cf::launch_backward(b, m->nw, m->block_backward[l], m->lds_backward[l], s);
   if (e != hipSuccess) return set_err(CF_E_DEVICE, std::string("backward launch: ") + hipGetErrorString(e));
+  return CF_OK;
+}
+
+cf_status cf_rollout_backward(cf_model *m, void *stream, int32_t T, const float *q_traj, const float *v_traj,
+                              const float *tau_seq, const float *gq_traj, const float *gv_traj, float *gq0,
+                              float *gv0, float *gtau_seq) {
+  if (!m) return set_err(CF_E_INVALID_ARG, "model is NULL");
+  if (T < 1) return set_err(CF_E_INVALID_ARG, "T must be >= 1");
+  if (!q_traj || !v_traj || !gq0 || !gv0) return set_err(CF_E_INVALID_ARG, "q_traj, v_traj, gq0, gv0 must be non-NULL");
+  const size_t sq = (size_t)m->nw * m->nq, sv = (size_t)m->nw * m->nv;
+  const float *ptrs[] = {q_traj, v_traj, tau_seq, gq_traj, gv_traj, gq0, gv0, gtau_seq};
+  for (const float *p : ptrs)
+    if (p && !aligned16(p)) return set_err(CF_E_INVALID_ARG, "buffers must be 16-byte aligned");
+  if (T > 1 && (sq % 4 || sv % 4)) return set_err(CF_E_INVALID_ARG, "trajectory rows must be 16-byte aligned");
+  auto overlap = [](const float *x, size_t nx, const float *y, size_t ny) {
+    return x && y && x < y + ny && y < x + nx;
+  };
+  const size_t nq = (T + 1) * sq, nv = (T + 1) * sv, nt = T * sv;
+  struct Span { const float *p; size_t n; };
+  const Span in[] = {{q_traj, nq}, {v_traj, nv}, {tau_seq, nt}, {gq_traj, nq}, {gv_traj, nv}};
+  const Span out[] = {{gq0, sq}, {gv0, sv}, {gtau_seq, nt}};
+  for (int i = 0; i < 3; ++i) {
+    for (const auto &x : in)
+      if (overlap(out[i].p, out[i].n, x.p, x.n)) return set_err(CF_E_INVALID_ARG, "outputs must not overlap inputs");
+    for (int j = 0; j < i; ++j)
+      if (overlap(out[i].p, out[i].n, out[j].p, out[j].n)) return set_err(CF_E_INVALID_ARG, "outputs must not overlap");
+  }
+  if (const cf_status st = adjoint_supported(m); st != CF_OK) return st;
+  hipStream_t s = (hipStream_t)stream;
+  const float *gqT = gq_traj ? gq_traj + T * sq : nullptr, *gvT = gv_traj ? gv_traj + T * sv : nullptr;
+  if (adjoint_free(m, T)) {
+    cf::AdjointArgs r = adjoint_args(m);
+    r.q_traj = q_traj; r.v_traj = v_traj; r.tau_seq = tau_seq;
+    r.gq_end = gqT; r.gv_end = gvT; r.gq_add = gq_traj; r.gv_add = gv_traj;
+    r.gq = gq0; r.gv = gv0; r.gtau = gtau_seq; r.T = T;
+    const hipError_t e = cf::launch_adjoint_free(r, m->lds_adjoint_free, s);
+    if (e != hipSuccess) return set_err(CF_E_DEVICE, std::string("adjoint launch: ") + hipGetErrorString(e));
+    return CF_OK;
+  }
+  for (int t = T - 1; t >= 0; --t) {
+    const bool last = t == T - 1;
+    const cf_status st = cf_step_backward(m, stream, q_traj + t * sq, v_traj + t * sv, tau_seq ? tau_seq + t * sv : nullptr,
+                                          last ? gqT : gq0, last ? gvT : gv0, gq0, gv0,
+                                          gtau_seq ? gtau_seq + t * sv : nullptr);
+    if (st != CF_OK) return st;
+    hipError_t e = hipSuccess;
+    if (gq_traj) e = cf::launch_add_rows(gq0, gq_traj + t * sq, sq, s);
+    if (e == hipSuccess && gv_traj) e = cf::launch_add_rows(gv0, gv_traj + t * sv, sv, s);
+    if (e != hipSuccess) return set_err(CF_E_DEVICE, std::string("adjoint sum launch: ") + hipGetErrorString(e));
+  }
   return CF_OK;
 }
 

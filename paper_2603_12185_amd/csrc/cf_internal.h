@@ -159,6 +159,21 @@ struct BackwardArgs {
   float *gq, *gv, *gtau;        // [nw][nq], [nw][nv], [nw][nv] (gtau may be null)
 };
 
+// Adjoint of T consecutive steps (free bodies, one wave per world): the
+// states at the start of each step and the step inputs, [T] rows; the adjoints
+// of the state after the last step, and adjoints added to those of each state
+// t = T - 1 .. 0 (each null = 0); out: the adjoints of state 0 and of every
+// step input (gtau may be null).
+struct AdjointArgs {
+  CollideArgs c;                // q and counts unused
+  BackwardArgs b;               // per-step pointers unused
+  const float *q_traj, *v_traj, *tau_seq;
+  const float *gq_end, *gv_end, *gq_add, *gv_add;
+  float *gq, *gv, *gtau;
+  int T, nworld;
+  int con, con_ofs;             // contact records held in LDS (0: the workspace), and where (set by the launch)
+};
+
 // Learned gains: bytes of the network's LDS image, and the kernel writing it
 // from the float32 parameters (one workgroup).
 size_t mlp_image_bytes();
@@ -169,6 +184,12 @@ size_t backward_lds_bytes(int nq, int nv, int nb, int ng, int block, int nsub, i
 // bodies (small: SubTree::small).
 int art_backward_floats(int nd, int nbs, bool small);
 hipError_t launch_backward(const BackwardArgs &a, int nworld, int block, size_t lds, hipStream_t s);
+
+// One-wave worlds of at most 64 free bodies; con: contact records in LDS.
+size_t adjoint_free_lds_bytes(int nq, int nb, int ng, int norient, int nsph, int con);
+hipError_t launch_adjoint_free(AdjointArgs a, size_t lds, hipStream_t s);
+// x += y, n floats.
+hipError_t launch_add_rows(float *x, const float *y, size_t n, hipStream_t s);
 
 size_t collide_lds_bytes(int nq, int nb, int ng, int norient, int nsub, int nsph);
 size_t rollout_lds_bytes(int nq, int nv, int nb, int ng, int norient, int nsub, int nsph, int art_floats, int cap);

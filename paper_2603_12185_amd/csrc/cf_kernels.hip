@@ -2675,28 +2675,43 @@ __device__ inline FreeGeomPre free_geom_prefetch(const ResolveArgs &a, int w, in
   return G;
 }
 
-// Resolution of world w of free bodies, lane b owning body b: from the lane's
-// q (7), v (6) and applied-force (6) entries and mass/inertia, the world's nc
-// contacts (the first chunk's records cn, cp of lane threadIdx.x already
-// loaded by the caller, the rest read from cnp/cpos), to the lane's q+ and v+
-// (qo, vo; lanes beyond nb return zeros).  `lds`: resolve_free_lds_bytes();
-// `xbase`: row of the world in the export arrays; `gpre`: the caller's
-// free_geom_prefetch of world w, or null.  Ends with a workgroup barrier after
-// the last read of the body arrays.
+// LDS of the free-body resolution (resolve_free_lds_bytes()): per body (COM |
+// 1/m), (v_s | 3/m), (w_s | -) and the inverse world inertia, the fixed-point
+// sums, and per geom its body and friction.
+struct FreeRegion {
+  float4 *bC, *bV, *bW, *bI0, *bI1, *gM;
+  int *fx, *gB;
+};
+__device__ inline FreeRegion free_region(float4 *lds, int nb, int ng) {
+  FreeRegion R;
+  R.bC = lds; R.bV = R.bC + nb; R.bW = R.bV + nb; R.bI0 = R.bW + nb; R.bI1 = R.bI0 + nb;
+  R.fx = reinterpret_cast<int *>(R.bI1 + nb);
+  R.gB = R.fx + 8 * pad4(nb);
+  R.gM = reinterpret_cast<float4 *>(R.gB + pad4(ng));
+  return R;
+}
+
+// Prediction and contact wrench sums of world w of free bodies, lane b owning
+// body b: from the lane's q (7), v (6) and applied-force (6) entries and
+// mass/inertia and the world's nc contacts (the first chunk's records cn, cp of
+// lane threadIdx.x already loaded by the caller, the rest read from cnp/cpos)
+// to the force F and torque T on the lane's body.  `lds`:
+// resolve_free_lds_bytes(), left holding free_region's arrays; `xbase`: row of
+// the world in the export arrays; `gpre`: the caller's free_geom_prefetch of
+// world w, or null.  Ends with a workgroup barrier.
 template <int CONDIM, int BS>
-__device__ void resolve_free_world(const ResolveArgs &a, int w, const float *qb, const float *vb, const float *tb,
-                                   float4 mi, int nc, float4 cn, float4 cp, const float4 *cnp, const float4 *cpos,
-                                   size_t xbase, float4 *lds, float *qo, float *vo, int tid_in = -1,
-                                   const FreeGeomPre *gpre = nullptr) {
+__device__ void resolve_free_sums(const ResolveArgs &a, int w, const float *qb, const float *vb, const float *tb,
+                                  float4 mi, int nc, float4 cn, float4 cp, const float4 *cnp, const float4 *cpos,
+                                  size_t xbase, float4 *lds, float4 &F, float4 &T, int tid, const FreeGeomPre *gpre) {
   constexpr int NF = CONDIM == 1 ? 1 : CONDIM == 3 ? 4 : CONDIM == 4 ? 6 : 10;
-  const int tid = tid_in >= 0 ? tid_in : (int)threadIdx.x;
   const int nb = a.nb, ng = a.ng, nbp = pad4(nb);
-  float4 *bC = lds, *bV = bC + nb, *bW = bV + nb, *bI0 = bW + nb, *bI1 = bI0 + nb;
-  int *fx = reinterpret_cast<int *>(bI1 + nb);
+  const FreeRegion R = free_region(lds, nb, ng);
+  float4 *bC = R.bC, *bV = R.bV, *bW = R.bW, *bI0 = R.bI0, *bI1 = R.bI1;
+  int *fx = R.fx;
   int *fxE = fx + 6 * nbp;
   unsigned long long *fxQ = reinterpret_cast<unsigned long long *>(fx);  // [3][nbp] packed sums
-  int *gB = fx + 8 * nbp;
-  float4 *gM = reinterpret_cast<float4 *>(gB + pad4(ng));
+  int *gB = R.gB;
+  float4 *gM = R.gM;
   const Params P = a.p;
   const bool own = tid < nb;
   {
@@ -2720,7 +2735,7 @@ __device__ void resolve_free_world(const ResolveArgs &a, int w, const float *qb,
   }
   for (int i = tid; i < 8 * nbp; i += BS) fx[i] = i >= 6 * nbp ? FX_EMPTY : 0;
   if (own) free_body_predict(qb, vb, tb, mi, P, bC[tid], bV[tid], bW[tid], bI0[tid], bI1[tid]);
-  float4 F = make_float4(0.f, 0.f, 0.f, 0.f), T = F;  // the lane's body: accumulated force and torque
+  F = T = make_float4(0.f, 0.f, 0.f, 0.f);  // the lane's body: accumulated force and torque
   __syncthreads();
 
   const float aa = P.k_user * P.h + P.d_user;
@@ -2795,13 +2810,27 @@ __device__ void resolve_free_world(const ResolveArgs &a, int w, const float *qb,
     cn = nn;
     cp = np;
   }
+}
 
-  // velocity correction and integration of the lane's body
+// Resolution of world w of free bodies, lane b owning body b: resolve_free_sums,
+// then velocity correction and integration to the lane's q+ and v+ (qo, vo;
+// lanes beyond nb return zeros).  Ends with a workgroup barrier after the last
+// read of the body arrays.
+template <int CONDIM, int BS>
+__device__ void resolve_free_world(const ResolveArgs &a, int w, const float *qb, const float *vb, const float *tb,
+                                   float4 mi, int nc, float4 cn, float4 cp, const float4 *cnp, const float4 *cpos,
+                                   size_t xbase, float4 *lds, float *qo, float *vo, int tid_in = -1,
+                                   const FreeGeomPre *gpre = nullptr) {
+  const int tid = tid_in >= 0 ? tid_in : (int)threadIdx.x;
+  const FreeRegion R = free_region(lds, a.nb, a.ng);
+  float4 F, T;
+  resolve_free_sums<CONDIM, BS>(a, w, qb, vb, tb, mi, nc, cn, cp, cnp, cpos, xbase, lds, F, T, tid, gpre);
 #pragma unroll
   for (int i = 0; i < 7; ++i) qo[i] = 0.f;
 #pragma unroll
   for (int i = 0; i < 6; ++i) vo[i] = 0.f;
-  if (own) free_body_correct(bC[tid], bV[tid], bW[tid], bI0[tid], bI1[tid], F, T, qb, P, qo, vo);
+  if (tid < a.nb)
+    free_body_correct(R.bC[tid], R.bV[tid], R.bW[tid], R.bI0[tid], R.bI1[tid], F, T, qb, a.p, qo, vo);
   __syncthreads();
 }
 
@@ -4110,6 +4139,156 @@ __device__ float small_phi_dir(const SubTree S, const SmallChain &C, int k, int 
   return phi;
 }
 
+// Reverse of one contact: its impulses, wrench and geometry (record cn, cp),
+// from the adjoints bFb, bTb of the bodies' force and torque sums, to the two
+// bodies' adjoints: keys kA, kB (left alone for a static side) and per side
+// (x bar, psi bar, v_s bar, w_s bar | trace bar) as four packed float4.  gB, gM,
+// bC .. bI1: the resolution's LDS arrays; body_frame(body, R, origin): rotation
+// and frame origin at the start of the step; radius(geom): size 0 of a geom.
+template <int NF, bool NET, class Frame, class Radius>
+__device__ inline void contact_reverse(const BackwardArgs &b, int w, float4 cn, float4 cp, const int *gB,
+                                       const float4 *gM, const float4 *bC, const float4 *bV, const float4 *bW,
+                                       const float4 *bI0, const float4 *bI1, const float4 *bFb, const float4 *bTb,
+                                       const adj::Impedance<float> &I, Frame body_frame, Radius radius, int &kA,
+                                       int &kB, float4 *pA, float4 *pB) {
+  using adj::Vec;
+  using adj::vec;
+  const ResolveArgs &a = b.s;
+  const Params &P = a.p;
+  auto xyz = [](float4 f) { return vec(f.x, f.y, f.z); };
+  const uint32_t sl = __float_as_uint(cp.w);
+  const int ga = slot_ga(sl), gb = slot_gb(sl);
+  const uint32_t type = slot_type(sl);
+  const int ba = gB[ga], bbd = gB[gb];
+  adj::ContactIn<float> C;
+  const Vec<float> Z = vec(0.f, 0.f, 0.f);
+  C.n = vec(cn.x, cn.y, cn.z); C.p = vec(cp.x, cp.y, cp.z); C.phi = cn.w;
+  C.xa = C.va = C.wa = C.xb = C.vb = C.wb = Z;
+  C.has_a = ba >= 0; C.has_b = bbd >= 0;
+  C.trs = 0.f;
+  if (ba >= 0) { C.xa = xyz(bC[ba]); C.va = xyz(bV[ba]); C.wa = xyz(bW[ba]); C.trs += bV[ba].w; }
+  if (bbd >= 0) { C.xb = xyz(bC[bbd]); C.vb = xyz(bV[bbd]); C.wb = xyz(bW[bbd]); C.trs += bV[bbd].w; }
+  const float4 ma = gM[ga], mb = gM[gb];
+  C.mut = fmaxf(ma.x, mb.x); C.mutor = fmaxf(ma.y, mb.y); C.murol = fmaxf(ma.z, mb.z);
+  C.h = P.h; C.k = P.k_user; C.d = P.d_user;
+  C.diag = P.imp_diag != 0;
+  C.net = NET ? a.mlp : nullptr;  // learned gains (free bodies): the float32 network
+  C.margin = P.mlp_margin;
+  C.ima = C.imb = 0.f;
+  if (C.diag) {  // free bodies only: 1/m and the world inverse inertia at the step's start
+    auto inertia = [&](int bi, float *S) {
+      const float4 I0 = bI0[bi], I1 = bI1[bi];
+      S[0] = I0.x; S[1] = I0.y; S[2] = I0.z; S[3] = I0.w; S[4] = I1.x; S[5] = I1.y;
+    };
+    if (ba >= 0) { C.ima = bC[ba].w; inertia(ba, C.Sa); }
+    if (bbd >= 0) { C.imb = bC[bbd].w; inertia(bbd, C.Sb); }
+  }
+  const Vec<float> Fab = ba >= 0 ? xyz(bFb[ba]) : Z, Tab = ba >= 0 ? xyz(bTb[ba]) : Z;
+  const Vec<float> Fbb = bbd >= 0 ? xyz(bFb[bbd]) : Z, Tbb = bbd >= 0 ? xyz(bTb[bbd]) : Z;
+  adj::ContactBar<float> o;
+  adj::contact_vjp<NF, float, NET>(C, I, Fab, Tab, Fbb, Tbb, o);
+  // geometry: contact (n, phi, p) from the two geoms' poses
+  Vec<float> xab = o.xa, xbb = o.xb, psa = Z, psb = Z;
+  const Vec<float> n = C.n, p = C.p;
+  const float phi = C.phi;
+  if (type == kSphereSphere) {
+    const float ra = radius(ga), rb = radius(gb);
+    Vec<float> cab, cbb;
+    adj::sphere_pair_vjp(n, phi, ra, rb, o.n, o.phi, o.p, cab, cbb);
+    const Vec<float> ca = p - (ra + 0.5f * phi) * n;
+    const Vec<float> cb = ca + (phi + ra + rb) * n;
+    xab = xab + cab; psa = adj::cross(ca - C.xa, cab);
+    xbb = xbb + cbb; psb = adj::cross(cb - C.xb, cbb);
+  } else if (type == kBoxSphere || type == kBoxCapsule) {
+    // box (geom a) against the sphere centre or capsule end c of geom b; the
+    // region of c (axes outside the box) picks the face plane, the edge
+    // line or the corner the forward gap was measured from
+    const float rad = radius(gb);
+    const Vec<float> c = p + (rad + 0.5f * phi) * n;
+    float Rb[9] = {1.f, 0.f, 0.f, 0.f, 1.f, 0.f, 0.f, 0.f, 1.f}, Rg[9], RX[9];
+    Vec<float> xo = Z;
+    if (ba >= 0) body_frame(ba, Rb, xo);
+    const float4 o4 = b.gpos[(size_t)w * b.gpos_ws + ga], g4 = b.gquat[(size_t)w * b.gquat_ws + ga];
+    quat_to_rot<float>(g4.x, g4.y, g4.z, g4.w, Rg);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) RX[3 * i + j] = Rb[3 * i] * Rg[j] + Rb[3 * i + 1] * Rg[3 + j] + Rb[3 * i + 2] * Rg[6 + j];
+    const Vec<float> X = xo + vec(Rb[0] * o4.x + Rb[1] * o4.y + Rb[2] * o4.z, Rb[3] * o4.x + Rb[4] * o4.y + Rb[5] * o4.z,
+                                  Rb[6] * o4.x + Rb[7] * o4.y + Rb[8] * o4.z);
+    const float4 gda = a.gdat[(size_t)w * a.ng + ga];
+    const float hs[3] = {gda.x, gda.y, gda.z};
+    const Vec<float> dc = c - X;
+    Vec<float> corner = X, e0 = X, u = Z;
+    int nout = 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const Vec<float> col = vec(RX[k], RX[3 + k], RX[6 + k]);
+      const float l = adj::dot(col, dc);
+      const float sh = (l >= 0.f ? hs[k] : -hs[k]);
+      corner = corner + sh * col;
+      if (fabsf(l) > hs[k]) {
+        ++nout;
+        e0 = e0 + sh * col;
+      } else {
+        u = col;
+      }
+    }
+    Vec<float> cbar, abx, abp;
+    if (nout <= 1) {  // face or inside: the plane of the face
+      const Vec<float> pp = c - (phi + rad) * n;
+      Vec<float> ppb, nnb;
+      adj::plane_point_vjp(pp, n, c, rad, phi, o.n, o.phi, o.p, cbar, ppb, nnb);
+      abx = ppb;
+      abp = adj::cross(pp - C.xa, ppb) + adj::cross(n, nnb);
+    } else if (nout == 2) {  // edge along the axis where c lies within the box
+      Vec<float> e0b, ub;
+      adj::line_point_vjp(e0, u, c, rad, n, phi, o.n, o.phi, o.p, cbar, e0b, ub);
+      abx = e0b;
+      abp = adj::cross(e0 - C.xa, e0b) + adj::cross(u, ub);
+    } else {  // corner: a sphere of radius 0
+      Vec<float> cab;
+      adj::sphere_pair_vjp(n, phi, 0.f, rad, o.n, o.phi, o.p, cab, cbar);
+      abx = cab;
+      abp = adj::cross(corner - C.xa, cab);
+    }
+    xbb = xbb + cbar; psb = adj::cross(c - C.xb, cbar);
+    if (ba >= 0) { xab = xab + abx; psa = abp; }
+  } else {
+    const float rad = type == kPlaneBox ? 0.f : radius(gb);
+    const Vec<float> c = p + (rad + 0.5f * phi) * n;
+    Vec<float> pp = c - (phi + rad) * n;  // a point of the plane (static plane: n is fixed)
+    if (ba >= 0) {
+      float R[9];
+      Vec<float> xo;
+      body_frame(ba, R, xo);
+      const float4 o4 = b.gpos[(size_t)w * b.gpos_ws + ga];
+      pp = xo + vec(R[0] * o4.x + R[1] * o4.y + R[2] * o4.z, R[3] * o4.x + R[4] * o4.y + R[5] * o4.z,
+                    R[6] * o4.x + R[7] * o4.y + R[8] * o4.z);
+    }
+    Vec<float> cbar, ppb, nnb;
+    adj::plane_point_vjp(pp, n, c, rad, phi, o.n, o.phi, o.p, cbar, ppb, nnb);
+    xbb = xbb + cbar; psb = adj::cross(c - C.xb, cbar);
+    if (ba >= 0) { xab = xab + ppb; psa = adj::cross(pp - C.xa, ppb) + adj::cross(n, nnb); }
+  }
+  psa = psa + o.psa;
+  psb = psb + o.psb;
+  if (ba >= 0) {
+    kA = ba;
+    pA[0] = make_float4(xab.x, xab.y, xab.z, psa.x);
+    pA[1] = make_float4(psa.y, psa.z, o.va.x, o.va.y);
+    pA[2] = make_float4(o.va.z, o.wa.x, o.wa.y, o.wa.z);
+    pA[3] = make_float4(o.trs, 0.f, 0.f, 0.f);
+  }
+  if (bbd >= 0) {
+    kB = bbd;
+    pB[0] = make_float4(xbb.x, xbb.y, xbb.z, psb.x);
+    pB[1] = make_float4(psb.y, psb.z, o.vb.x, o.vb.y);
+    pB[2] = make_float4(o.vb.z, o.wb.x, o.wb.y, o.wb.z);
+    pB[3] = make_float4(o.trs, 0.f, 0.f, 0.f);
+  }
+}
+
 // Reverse of one step of world w: the forward step is recomputed in LDS
 // (same code as the resolution kernel, so the same contact set, facet
 // activity and branches), then the adjoints run backwards through
@@ -4234,140 +4413,10 @@ __global__ __launch_bounds__(BS) void backward_kernel(BackwardArgs b) {
     float4 pA[4], pB[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) pA[i] = pB[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (k < nc) {
-      const float4 cn = a.cnp[cbase + k], cp = a.cpos[cbase + k];
-      const uint32_t sl = __float_as_uint(cp.w);
-      const int ga = slot_ga(sl), gb = slot_gb(sl);
-      const uint32_t type = slot_type(sl);
-      const int ba = RR.gB[ga], bbd = RR.gB[gb];
-      adj::ContactIn<float> C;
-      const Vec<float> Z = vec(0.f, 0.f, 0.f);
-      C.n = vec(cn.x, cn.y, cn.z); C.p = vec(cp.x, cp.y, cp.z); C.phi = cn.w;
-      C.xa = C.va = C.wa = C.xb = C.vb = C.wb = Z;
-      C.has_a = ba >= 0; C.has_b = bbd >= 0;
-      C.trs = 0.f;
-      if (ba >= 0) { C.xa = xyz(RR.bC[ba]); C.va = xyz(RR.bV[ba]); C.wa = xyz(RR.bW[ba]); C.trs += RR.bV[ba].w; }
-      if (bbd >= 0) { C.xb = xyz(RR.bC[bbd]); C.vb = xyz(RR.bV[bbd]); C.wb = xyz(RR.bW[bbd]); C.trs += RR.bV[bbd].w; }
-      const float4 ma = RR.gM[ga], mb = RR.gM[gb];
-      C.mut = fmaxf(ma.x, mb.x); C.mutor = fmaxf(ma.y, mb.y); C.murol = fmaxf(ma.z, mb.z);
-      C.h = P.h; C.k = P.k_user; C.d = P.d_user;
-      C.diag = P.imp_diag != 0;
-      C.net = NET ? a.mlp : nullptr;  // learned gains (free bodies): the float32 network
-      C.margin = P.mlp_margin;
-      C.ima = C.imb = 0.f;
-      if (C.diag) {  // free bodies only: 1/m and the world inverse inertia at the step's start
-        auto inertia = [&](int bi, float *S) {
-          const float4 I0 = RR.bI0[bi], I1 = RR.bI1[bi];
-          S[0] = I0.x; S[1] = I0.y; S[2] = I0.z; S[3] = I0.w; S[4] = I1.x; S[5] = I1.y;
-        };
-        if (ba >= 0) { C.ima = RR.bC[ba].w; inertia(ba, C.Sa); }
-        if (bbd >= 0) { C.imb = RR.bC[bbd].w; inertia(bbd, C.Sb); }
-      }
-      const Vec<float> Fab = ba >= 0 ? xyz(bFb[ba]) : Z, Tab = ba >= 0 ? xyz(bTb[ba]) : Z;
-      const Vec<float> Fbb = bbd >= 0 ? xyz(bFb[bbd]) : Z, Tbb = bbd >= 0 ? xyz(bTb[bbd]) : Z;
-      adj::ContactBar<float> o;
-      adj::contact_vjp<NF, float, NET>(C, I, Fab, Tab, Fbb, Tbb, o);
-      // geometry: contact (n, phi, p) from the two geoms' poses
-      Vec<float> xab = o.xa, xbb = o.xb, psa = Z, psb = Z;
-      const float4 gda = a.gdat[(size_t)w * ng + ga], gdb = a.gdat[(size_t)w * ng + gb];
-      const Vec<float> n = C.n, p = C.p;
-      const float phi = C.phi;
-      if (type == kSphereSphere) {
-        const float ra = gda.x, rb = gdb.x;
-        Vec<float> cab, cbb;
-        adj::sphere_pair_vjp(n, phi, ra, rb, o.n, o.phi, o.p, cab, cbb);
-        const Vec<float> ca = p - (ra + 0.5f * phi) * n;
-        const Vec<float> cb = ca + (phi + ra + rb) * n;
-        xab = xab + cab; psa = adj::cross(ca - C.xa, cab);
-        xbb = xbb + cbb; psb = adj::cross(cb - C.xb, cbb);
-      } else if (type == kBoxSphere || type == kBoxCapsule) {
-        // box (geom a) against the sphere centre or capsule end c of geom b; the
-        // region of c (axes outside the box) picks the face plane, the edge
-        // line or the corner the forward gap was measured from
-        const float rad = gdb.x;
-        const Vec<float> c = p + (rad + 0.5f * phi) * n;
-        float Rb[9] = {1.f, 0.f, 0.f, 0.f, 1.f, 0.f, 0.f, 0.f, 1.f}, Rg[9], RX[9];
-        Vec<float> xo = Z;
-        if (ba >= 0) body_frame(ba, Rb, xo);
-        const float4 o4 = b.gpos[(size_t)w * b.gpos_ws + ga], g4 = b.gquat[(size_t)w * b.gquat_ws + ga];
-        quat_to_rot<float>(g4.x, g4.y, g4.z, g4.w, Rg);
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-          for (int j = 0; j < 3; ++j) RX[3 * i + j] = Rb[3 * i] * Rg[j] + Rb[3 * i + 1] * Rg[3 + j] + Rb[3 * i + 2] * Rg[6 + j];
-        const Vec<float> X = xo + vec(Rb[0] * o4.x + Rb[1] * o4.y + Rb[2] * o4.z, Rb[3] * o4.x + Rb[4] * o4.y + Rb[5] * o4.z,
-                                      Rb[6] * o4.x + Rb[7] * o4.y + Rb[8] * o4.z);
-        const float hs[3] = {gda.x, gda.y, gda.z};
-        const Vec<float> dc = c - X;
-        Vec<float> corner = X, e0 = X, u = Z;
-        int nout = 0;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          const Vec<float> col = vec(RX[k], RX[3 + k], RX[6 + k]);
-          const float l = adj::dot(col, dc);
-          const float sh = (l >= 0.f ? hs[k] : -hs[k]);
-          corner = corner + sh * col;
-          if (fabsf(l) > hs[k]) {
-            ++nout;
-            e0 = e0 + sh * col;
-          } else {
-            u = col;
-          }
-        }
-        Vec<float> cbar, abx, abp;
-        if (nout <= 1) {  // face or inside: the plane of the face
-          const Vec<float> pp = c - (phi + rad) * n;
-          Vec<float> ppb, nnb;
-          adj::plane_point_vjp(pp, n, c, rad, phi, o.n, o.phi, o.p, cbar, ppb, nnb);
-          abx = ppb;
-          abp = adj::cross(pp - C.xa, ppb) + adj::cross(n, nnb);
-        } else if (nout == 2) {  // edge along the axis where c lies within the box
-          Vec<float> e0b, ub;
-          adj::line_point_vjp(e0, u, c, rad, n, phi, o.n, o.phi, o.p, cbar, e0b, ub);
-          abx = e0b;
-          abp = adj::cross(e0 - C.xa, e0b) + adj::cross(u, ub);
-        } else {  // corner: a sphere of radius 0
-          Vec<float> cab;
-          adj::sphere_pair_vjp(n, phi, 0.f, rad, o.n, o.phi, o.p, cab, cbar);
-          abx = cab;
-          abp = adj::cross(corner - C.xa, cab);
-        }
-        xbb = xbb + cbar; psb = adj::cross(c - C.xb, cbar);
-        if (ba >= 0) { xab = xab + abx; psa = abp; }
-      } else {
-        const float rad = type == kPlaneBox ? 0.f : gdb.x;
-        const Vec<float> c = p + (rad + 0.5f * phi) * n;
-        Vec<float> pp = c - (phi + rad) * n;  // a point of the plane (static plane: n is fixed)
-        if (ba >= 0) {
-          float R[9];
-          Vec<float> xo;
-          body_frame(ba, R, xo);
-          const float4 o4 = b.gpos[(size_t)w * b.gpos_ws + ga];
-          pp = xo + vec(R[0] * o4.x + R[1] * o4.y + R[2] * o4.z, R[3] * o4.x + R[4] * o4.y + R[5] * o4.z,
-                        R[6] * o4.x + R[7] * o4.y + R[8] * o4.z);
-        }
-        Vec<float> cbar, ppb, nnb;
-        adj::plane_point_vjp(pp, n, c, rad, phi, o.n, o.phi, o.p, cbar, ppb, nnb);
-        xbb = xbb + cbar; psb = adj::cross(c - C.xb, cbar);
-        if (ba >= 0) { xab = xab + ppb; psa = adj::cross(pp - C.xa, ppb) + adj::cross(n, nnb); }
-      }
-      psa = psa + o.psa;
-      psb = psb + o.psb;
-      if (ba >= 0) {
-        kA = ba;
-        pA[0] = make_float4(xab.x, xab.y, xab.z, psa.x);
-        pA[1] = make_float4(psa.y, psa.z, o.va.x, o.va.y);
-        pA[2] = make_float4(o.va.z, o.wa.x, o.wa.y, o.wa.z);
-        pA[3] = make_float4(o.trs, 0.f, 0.f, 0.f);
-      }
-      if (bbd >= 0) {
-        kB = bbd;
-        pB[0] = make_float4(xbb.x, xbb.y, xbb.z, psb.x);
-        pB[1] = make_float4(psb.y, psb.z, o.vb.x, o.vb.y);
-        pB[2] = make_float4(o.vb.z, o.wb.x, o.wb.y, o.wb.z);
-        pB[3] = make_float4(o.trs, 0.f, 0.f, 0.f);
-      }
-    }
+    if (k < nc)
+      contact_reverse<NF, NET>(
+          b, w, a.cnp[cbase + k], a.cpos[cbase + k], RR.gB, RR.gM, RR.bC, RR.bV, RR.bW, RR.bI0, RR.bI1, bFb, bTb, I,
+          body_frame, [&](int g) { return a.gdat[(size_t)w * ng + g].x; }, kA, kB, pA, pB);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       pay[i * BS + tid] = pA[i];
@@ -4474,6 +4523,254 @@ hipError_t launch_backward(const BackwardArgs &a, int nworld, int block, size_t 
   if (a.s.nsub > 0) return a.s.mlp ? hipErrorInvalidValue : launch_backward_a<true, false>(a, nworld, block, lds, s);
   return a.s.mlp ? launch_backward_a<false, true>(a, nworld, block, lds, s)
                  : launch_backward_a<false, false>(a, nworld, block, lds, s);
+}
+
+__global__ void add_rows_kernel(float *x, const float *y, size_t n) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) x[i] += y[i];
+}
+
+hipError_t launch_add_rows(float *x, const float *y, size_t n, hipStream_t s) {
+  if (n == 0) return hipSuccess;
+  hipLaunchKernelGGL(add_rows_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, x, y, n);
+  return hipGetLastError();
+}
+
+// ---- adjoint of T >= 1 steps of worlds of at most 64 free bodies: one
+// persistent one-wave workgroup per world, lane b holding body b's adjoints
+//
+// Per step, latest first: the narrow phase and the resolution's prediction and
+// contact sums from the stored state (collide_world, resolve_free_sums: the
+// step's own contact set, facet activity and branches), then the reverse of
+// integration and correction, of the contacts (lane per contact) and of the
+// prediction.  A body's adjoint, state and sums stay in its lane's registers;
+// LDS holds what contact lanes read and the chunk's payloads, which each body
+// lane adds up itself in contact order, side a before side b, from the
+// chunk's masks of its contacts (integer ORs: order-free, so the sum is the
+// same run to run).  Bound by the latency of one wave's dependent chain (a step of five bodies is two
+// thousand instructions): launches, a second kernel's loads and idle waves
+// were most of the time of a step taken as collide_kernel + backward_kernel.
+// LDSC: the contact records stay in LDS (AdjointArgs::con of them).
+size_t adjoint_free_lds_bytes(int nq, int nb, int ng, int norient, int nsph, int con) {
+  const size_t c = collide_region_bytes(nb, ng, norient, 0, nsph);
+  const size_t r = resolve_free_lds_bytes(nb, ng) + sizeof(float) * pad4(ng) + sizeof(float4) * (2 * (size_t)nb + 6 * 64) +
+                   2 * sizeof(unsigned long long) * (size_t)nb;
+  return sizeof(float) * pad4(nq) + (c > r ? (c + 15) / 16 * 16 : (r + 15) / 16 * 16) + 2 * sizeof(float4) * (size_t)con;
+}
+
+template <int CONDIM, bool LDSC>
+__global__ __launch_bounds__(64, 1) void adjoint_free_kernel(AdjointArgs r) {
+  using adj::Vec;
+  using adj::vec;
+  constexpr int NF = CONDIM == 1 ? 1 : CONDIM == 3 ? 4 : CONDIM == 4 ? 6 : 10;
+  constexpr int BS = 64, K = 512 / BS;
+  extern __shared__ float4 lds[];
+  const CollideArgs &ca = r.c;
+  const ResolveArgs &a = r.b.s;
+  const int w = blockIdx.x, tid = threadIdx.x;
+  const int nq = a.nq, nv = a.nv, nb = a.nb, ng = a.ng, cap = ca.ncon_max;
+  const size_t sq_row = (size_t)r.nworld * nq, sv_row = (size_t)r.nworld * nv;
+  float *sq = reinterpret_cast<float *>(lds);
+  float4 *reg = lds + pad4(nq) / 4;
+  const FreeRegion FR = free_region(reg, nb, ng);
+  float *rad = reinterpret_cast<float *>(FR.gM + ng);                       // [ng] size 0 of each geom
+  float4 *bFb = reinterpret_cast<float4 *>(rad + pad4(ng)), *bTb = bFb + nb;
+  float4 *pay = bTb + nb;                                                     // [2][3][64]
+  unsigned long long *mask = reinterpret_cast<unsigned long long *>(pay + 6 * 64);  // [2][nb]
+  const bool own = tid < nb;
+  const int bl0 = own ? tid : nb - 1;
+  float gq[7], gv[6];
+#pragma unroll
+  for (int i = 0; i < 7; ++i) gq[i] = r.gq_end ? r.gq_end[(size_t)w * nq + 7 * bl0 + i] : 0.f;
+#pragma unroll
+  for (int i = 0; i < 6; ++i) gv[i] = r.gv_end ? r.gv_end[(size_t)w * nv + 6 * bl0 + i] : 0.f;
+  const Params P = a.p;
+  const adj::Impedance<float> I{P.r_min, P.r_max, P.width, P.mid, P.power};
+  auto xyz = [](float4 f) { return vec(f.x, f.y, f.z); };
+  // the state at the start of a step: the q row, the lane's body and input
+  RowStage<BS, K> rq;
+  float qb[7], vb[6], tb[6];
+  auto load_state = [&](int t, int wt, int bl) {
+    const float *qw = r.q_traj + t * sq_row + (size_t)wt * nq, *vw = r.v_traj + t * sv_row + (size_t)wt * nv;
+    rq.load(qw, nq);
+#pragma unroll
+    for (int i = 0; i < 7; ++i) qb[i] = qw[7 * bl + i];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) vb[i] = vw[6 * bl + i];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) tb[i] = r.tau_seq ? r.tau_seq[t * sv_row + (size_t)wt * nv + 6 * bl + i] : 0.f;
+  };
+  load_state(r.T - 1, w, bl0);
+  for (int t = r.T - 1; t >= 0; --t) {
+    // the world and lane index, opaque to the compiler in each step, so that
+    // what depends on them (addresses, the static geoms' poses) is formed where
+    // it is used instead of being held, and spilled, across the step loop
+    int wt = w, tl = tid;
+    asm volatile("" : "+s"(wt), "+v"(tl));
+    const int bl = own ? tl : nb - 1;
+    const size_t cbase = (size_t)wt * cap;
+    float4 *cnp = LDSC ? lds + r.con_ofs : ca.cnp + cbase, *cpos = LDSC ? cnp + r.con : ca.cpos + cbase;
+    const int wcap = LDSC ? min(cap, r.con) : cap;
+    // ---- forward step: every load before the first wait
+    const uint32_t nxt = ca.slots[tl < ca.nslot_pre ? tl : (ca.nslot_pre > 0 ? ca.nslot_pre - 1 : 0)];
+    const int gl = ng > 0 ? ng - 1 : 0;
+    const GeomIn pre[2] = {geom_in(ca, wt, tl < ng ? tl : gl), geom_in(ca, wt, tl + BS < ng ? tl + BS : gl)};
+    const FreeGeomPre gpre = free_geom_prefetch<CONDIM, BS>(a, wt, tl);
+    const float4 mi = a.bmi[(size_t)wt * nb + bl];
+    const float rad0 = pre[0].gd.x, rad1 = pre[1].gd.x;
+    rq.store(sq, r.q_traj + t * sq_row + (size_t)wt * nq, nq);
+    __syncthreads();
+    const int found = collide_world<BS, false>(ca, wt, sq, reg, cnp, cpos, wcap, nxt, pre, tl);
+    const int nc = found < wcap ? found : wcap;
+    const int r0 = tid < nc ? tid : (nc > 0 ? nc - 1 : 0);
+    __syncthreads();
+    const float4 c0n = cnp[r0], c0p = cpos[r0];
+    float4 F, T;
+    resolve_free_sums<CONDIM, BS>(a, wt, qb, vb, tb, mi, nc, c0n, c0p, cnp, cpos, 0, reg, F, T, tl, &gpre);
+    adj::BodyPredict<float> B;
+    B.m = mi.x; B.d[0] = mi.y; B.d[1] = mi.z; B.d[2] = mi.w;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) B.q[i] = qb[3 + i];
+    B.v = vec(vb[0], vb[1], vb[2]); B.w = vec(vb[3], vb[4], vb[5]);
+    B.f = vec(tb[0], tb[1], tb[2]); B.t = vec(tb[3], tb[4], tb[5]);
+    B.g = vec(P.gx, P.gy, P.gz); B.h = P.h;
+    // the previous step's state and the adjoints added to this one's, in
+    // flight through the reverse pass
+    load_state(t > 0 ? t - 1 : 0, wt, bl);
+    float gqa[7], gva[6];
+#pragma unroll
+    for (int i = 0; i < 7; ++i) gqa[i] = r.gq_add ? r.gq_add[t * sq_row + (size_t)wt * nq + 7 * bl + i] : 0.f;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) gva[i] = r.gv_add ? r.gv_add[t * sv_row + (size_t)wt * nv + 6 * bl + i] : 0.f;
+    // ---- reverse of integration and correction
+    Vec<float> xb, vsb, wsb, psi = vec(0.f, 0.f, 0.f);
+    float qbar[4] = {0.f, 0.f, 0.f, 0.f};
+    {
+      adj::BodyUpdate<float> U;
+      U.m = B.m;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) U.d[i] = B.d[i];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) U.q[i] = B.q[i];
+      U.x = xyz(FR.bC[bl]); U.vs = xyz(FR.bV[bl]); U.ws = xyz(FR.bW[bl]);
+      U.F = xyz(F); U.Tq = xyz(T); U.h = P.h;
+      Vec<float> Fb, Tb;
+      adj::update_vjp(U, vec(gq[0], gq[1], gq[2]), gq + 3, vec(gv[0], gv[1], gv[2]), vec(gv[3], gv[4], gv[5]), xb,
+                      qbar, vsb, wsb, Fb, Tb, psi);
+      if (own) {
+        bFb[tid] = make_float4(Fb.x, Fb.y, Fb.z, 0.f);
+        bTb[tid] = make_float4(Tb.x, Tb.y, Tb.z, 0.f);
+        mask[tid] = mask[nb + tid] = 0ull;
+      }
+    }
+    if (tid < ng) rad[tid] = rad0;
+    if (tid + BS < ng) rad[tid + BS] = rad1;
+    for (int g = tid + 2 * BS; g < ng; g += BS) rad[g] = ca.gdat[(size_t)wt * ng + g].x;
+    __syncthreads();
+    // ---- reverse of the contacts
+    auto body_frame = [&](int bi, float *R, Vec<float> &org) {
+      adj::rot_of_quat(sq + 7 * bi + 3, R);
+      org = xyz(FR.bC[bi]);
+    };
+    for (int base = 0; base < nc; base += BS) {
+      const int k = base + tid;
+      int kA = nb, kB = nb;
+      if (k < nc) {
+        float4 pA[4], pB[4];
+        contact_reverse<NF, false>(
+            r.b, wt, base == 0 ? c0n : cnp[k], base == 0 ? c0p : cpos[k], FR.gB, FR.gM, FR.bC, FR.bV, FR.bW, FR.bI0,
+            FR.bI1, bFb, bTb, I, body_frame, [&](int g) { return rad[g]; }, kA, kB, pA, pB);
+        if (kA < nb) {
+          atomicOr(mask + kA, 1ull << tid);
+#pragma unroll
+          for (int i = 0; i < 3; ++i) pay[i * BS + tid] = pA[i];
+        }
+        if (kB < nb) {
+          atomicOr(mask + nb + kB, 1ull << tid);
+#pragma unroll
+          for (int i = 0; i < 3; ++i) pay[(3 + i) * BS + tid] = pB[i];
+        }
+      }
+      __syncthreads();
+      if (own) {
+        float4 S[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) S[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        const unsigned long long mA = mask[tid], mB = mask[nb + tid];
+#pragma unroll
+        for (int side = 0; side < 2; ++side)
+          for (unsigned long long m = side ? mB : mA; m;) {
+            // two entries at a time: their loads in flight together
+            const int k0 = __ffsll(m) - 1;
+            m &= m - 1ull;
+            const int k1 = m ? __ffsll(m) - 1 : -1;
+            m &= m - 1ull;
+            const float4 *e = pay + 3 * BS * side;
+            float4 x[3], y[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+              x[i] = e[i * BS + k0];
+              y[i] = e[i * BS + (k1 >= 0 ? k1 : k0)];
+            }
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+              S[i].x += x[i].x; S[i].y += x[i].y; S[i].z += x[i].z; S[i].w += x[i].w;
+              if (k1 >= 0) {
+                S[i].x += y[i].x; S[i].y += y[i].y; S[i].z += y[i].z; S[i].w += y[i].w;
+              }
+            }
+          }
+        xb = xb + vec(S[0].x, S[0].y, S[0].z);
+        psi = psi + vec(S[0].w, S[1].x, S[1].y);
+        vsb = vsb + vec(S[1].z, S[1].w, S[2].x);
+        wsb = wsb + vec(S[2].y, S[2].z, S[2].w);
+        mask[tid] = mask[nb + tid] = 0ull;
+      }
+      __syncthreads();
+    }
+    // ---- reverse of the prediction; the adjoints of state t
+    Vec<float> vbar, wbar, fb, tbar;
+    adj::predict_vjp(B, vsb, wsb, vbar, wbar, fb, tbar, psi);
+    adj::quat_grad_from_psi(B.q, psi, qbar);
+    if (own && r.gtau) {
+      float *g = r.gtau + t * sv_row + (size_t)wt * nv + 6 * tl;
+      g[0] = fb.x; g[1] = fb.y; g[2] = fb.z; g[3] = tbar.x; g[4] = tbar.y; g[5] = tbar.z;
+    }
+    gq[0] = xb.x; gq[1] = xb.y; gq[2] = xb.z;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) gq[3 + i] = qbar[i];
+    gv[0] = vbar.x; gv[1] = vbar.y; gv[2] = vbar.z; gv[3] = wbar.x; gv[4] = wbar.y; gv[5] = wbar.z;
+#pragma unroll
+    for (int i = 0; i < 7; ++i) gq[i] += gqa[i];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) gv[i] += gva[i];
+  }
+  if (own) {
+    float *gqw = r.gq + (size_t)w * nq + 7 * tid, *gvw = r.gv + (size_t)w * nv + 6 * tid;
+#pragma unroll
+    for (int i = 0; i < 7; ++i) gqw[i] = gq[i];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) gvw[i] = gv[i];
+  }
+}
+
+template <bool LDSC>
+static hipError_t launch_adjoint_free_c(const AdjointArgs &a, size_t lds, hipStream_t s) {
+  switch (a.b.s.condim) {
+    case 1: hipLaunchKernelGGL((adjoint_free_kernel<1, LDSC>), dim3(a.nworld), dim3(64), lds, s, a); break;
+    case 3: hipLaunchKernelGGL((adjoint_free_kernel<3, LDSC>), dim3(a.nworld), dim3(64), lds, s, a); break;
+    case 4: hipLaunchKernelGGL((adjoint_free_kernel<4, LDSC>), dim3(a.nworld), dim3(64), lds, s, a); break;
+    case 6: hipLaunchKernelGGL((adjoint_free_kernel<6, LDSC>), dim3(a.nworld), dim3(64), lds, s, a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_adjoint_free(AdjointArgs a, size_t lds, hipStream_t s) {
+  const ResolveArgs &m = a.b.s;
+  if (m.nsub > 0 || m.mlp || m.act || m.nb < 1 || m.nb > 64 || a.T < 1) return hipErrorInvalidValue;
+  a.con_ofs = (int)(lds / sizeof(float4)) - 2 * a.con;
+  return a.con > 0 ? launch_adjoint_free_c<true>(a, lds, s) : launch_adjoint_free_c<false>(a, lds, s);
 }
 
 }  // namespace cf
