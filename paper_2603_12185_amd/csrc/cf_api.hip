@@ -875,9 +875,17 @@ cf_status cf_rollout(cf_model *m, void *stream, int32_t T, const float *q0, cons
     // the free-body kernel sized for three resident waves per SIMD (twelve
     // one-wave worlds per CU, no register spills) while the batch fits the
     // device at that occupancy, else for four
+    // one-wave worlds of articulated models keep their constants in LDS where
+    // eight worlds (two waves per SIMD) still share a CU's 160 KB with them
+    size_t lds = (m->lds_rollout + 15) / 16 * 16;
+    const size_t consts = cf::rollout_const_bytes(m->nb, m->ng, m->nv, m->nsub);
+    if (m->nsub > 0 && m->block_rollout == 64 && lds + consts <= 20 * 1024) {
+      r.const_ofs = (int)(lds / 16);
+      lds += consts;
+    }
     hipError_t e = rollout_free(m)
                        ? cf::launch_rollout_free(r, m->lds_rollout_free, m->nw <= 12 * m->ncu ? 3 : 4, s)
-                       : cf::launch_rollout(r, m->block_rollout, m->lds_rollout, s);
+                       : cf::launch_rollout(r, m->block_rollout, lds, s);
     if (e != hipSuccess) return set_err(CF_E_DEVICE, std::string("rollout launch: ") + hipGetErrorString(e));
     return CF_OK;
   }

@@ -147,6 +147,7 @@ struct RolloutArgs {
   int *ncon_traj;               // [T][nw] contacts kept per step, or null
   int *over_traj;               // [T][nw] contacts dropped beyond cap per step, or null
   int T, nworld, cap;           // cap: contacts held per world per step (= ncon_max)
+  int const_ofs;                // > 0: float4 offset in LDS of the world's model constants (rollout_const_bytes)
 };
 
 // Adjoint of one step (free bodies): one workgroup per world.
@@ -193,6 +194,7 @@ hipError_t launch_add_rows(float *x, const float *y, size_t n, hipStream_t s);
 
 size_t collide_lds_bytes(int nq, int nb, int ng, int norient, int nsub, int nsph);
 size_t rollout_lds_bytes(int nq, int nv, int nb, int ng, int norient, int nsub, int nsph, int art_floats, int cap);
+size_t rollout_const_bytes(int nb, int ng, int nv, int nsub);
 hipError_t launch_rollout(const RolloutArgs &a, int block, size_t lds, hipStream_t s);
 size_t resolve_lds_bytes(int nq, int nv, int nb, int ng, int nsub, int art_floats);
 size_t resolve_learned_lds_bytes(int block);  // extra LDS of the resolution with learned gains

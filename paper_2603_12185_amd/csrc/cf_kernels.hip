@@ -3345,11 +3345,26 @@ size_t rollout_lds_bytes(int nq, int nv, int nb, int ng, int norient, int nsub, 
   return sizeof(float) * (pad4(nq) + 2 * (size_t)pad4(nv)) + 2 * sizeof(float4) * (size_t)cap + (c > r ? c : r);
 }
 
-template <int CONDIM, int BS, bool ART>
+// Model constants of one world that rollout_kernel keeps in LDS over its steps
+// (LC): mass/inertia, small-subtree frames, actuators, geom offsets,
+// orientations, sizes and friction, body and subtree records.
+size_t rollout_const_bytes(int nb, int ng, int nv, int nsub) {
+  return sizeof(float4) * (6 * (size_t)nb + nv + 3 * (size_t)ng) + sizeof(float2) * (size_t)pad4(ng) +
+         3 * sizeof(int) * (size_t)pad4(ng) + sizeof(BodyC) * (size_t)nb + sizeof(int) * (size_t)pad4(10 * nsub);
+}
+static_assert(sizeof(BodyC) % sizeof(float4) == 0 && sizeof(SubTree) == 10 * sizeof(int), "records copied by words");
+
+// LC: a step's chain of dependent work is all that bounds a world (two waves
+// per SIMD at most), and every step began its phases by waiting for the same
+// constants from L2 and passed the subtrees' frames through it.
+// They are copied to LDS once and the narrow phase and the resolution read
+// them, and the frames, there (the same arithmetic, bit for bit): a batch of
+// 2048 hands and 20 steps FIGURE.
+template <int CONDIM, int BS, bool ART, bool LC>
 __global__ __launch_bounds__(BS, 2) void rollout_kernel(RolloutArgs r) {
   extern __shared__ float4 lds[];
-  const CollideArgs &ca = r.c;
-  const ResolveArgs &ra = r.s;
+  CollideArgs ca = r.c;
+  ResolveArgs ra = r.s;
   const int w = blockIdx.x, tid = threadIdx.x;
   const int nq = ra.nq, nv = ra.nv, nb = ra.nb, nw = r.nworld, cap = r.cap;
   float *sq = reinterpret_cast<float *>(lds);
@@ -3363,6 +3378,39 @@ __global__ __launch_bounds__(BS, 2) void rollout_kernel(RolloutArgs r) {
     for (int i = tid; i < nq; i += BS) sq[i] = qw[i];
     for (int i = tid; i < nv; i += BS) sv[i] = vw[i];
   }
+  int wc = w;  // the world's index in the model constants
+  if constexpr (LC) {
+    const int ng = ra.ng;
+    float4 *bmi = lds + r.const_ofs, *fr = bmi + nb, *act = fr + 5 * nb, *gpos = act + nv, *gquat = gpos + ng,
+           *gdat = gquat + ng, *body = gdat + ng;
+    int *sub = reinterpret_cast<int *>(body + nb * (int)(sizeof(BodyC) / sizeof(float4)));
+    float2 *gfr2 = reinterpret_cast<float2 *>(sub + pad4(10 * ra.nsub));
+    float *gmu = reinterpret_cast<float *>(gfr2 + pad4(ng));
+    int *gbody = reinterpret_cast<int *>(gmu + pad4(ng)), *gorient = gbody + pad4(ng);
+    for (int i = tid; i < nb; i += BS) bmi[i] = ra.bmi[(size_t)w * nb + i];
+    for (int i = tid; i < 5 * nb; i += BS) fr[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (ra.act)
+      for (int i = tid; i < nv; i += BS) act[i] = ra.act[i];
+    const float4 *bsrc = reinterpret_cast<const float4 *>(ra.body);
+    for (int i = tid; i < nb * (int)(sizeof(BodyC) / sizeof(float4)); i += BS) body[i] = bsrc[i];
+    const int *ssrc = reinterpret_cast<const int *>(ra.sub);
+    for (int i = tid; i < 10 * ra.nsub; i += BS) sub[i] = ssrc[i];
+    for (int g = tid; g < ng; g += BS) {
+      const GeomIn x = geom_in(ca, w, g);
+      gbody[g] = x.b; gorient[g] = x.o;
+      gpos[g] = x.gp; gquat[g] = x.gq; gdat[g] = x.gd;
+      gmu[g] = ra.gmu[(size_t)w * ng + g];
+      if (CONDIM >= 4) gfr2[g] = ra.gfr2[(size_t)w * ng + g];
+    }
+    ca.gpos = gpos; ca.gquat = gquat; ca.gdat = gdat; ca.gbody = gbody; ca.gorient = gorient;
+    ca.body = reinterpret_cast<const BodyC *>(body);
+    ca.sub = reinterpret_cast<const SubTree *>(sub);
+    if (ca.frames) ca.frames = fr;
+    ra.bmi = bmi; ra.gmu = gmu; ra.gfr2 = gfr2; ra.gbody = gbody; ra.body = ca.body; ra.sub = ca.sub;
+    if (ra.act) ra.act = act;
+    if (ra.frames) ra.frames = fr;
+    wc = 0;
+  }
   const uint32_t nxt = tid < ca.nslot_pre ? ca.slots[tid] : 0u;
   for (int t = 0; t < r.T; ++t) {
     if (r.tau_seq) {
@@ -3371,10 +3419,11 @@ __global__ __launch_bounds__(BS, 2) void rollout_kernel(RolloutArgs r) {
     } else {
       for (int i = tid; i < nv; i += BS) st[i] = 0.f;
     }
+    if (LC) __syncthreads();  // the constants are complete
     float4 mi0 = make_float4(1.f, 1.f, 1.f, 1.f);
-    if (tid < nb) mi0 = ra.bmi[(size_t)w * nb + tid];
+    if (tid < nb) mi0 = ra.bmi[(size_t)wc * nb + tid];
     __syncthreads();
-    const int found = collide_world<BS, ART>(ca, w, sq, reg, cn, cp, cap, nxt);
+    const int found = collide_world<BS, ART>(ca, wc, sq, reg, cn, cp, cap, nxt);
     const int nc = found < cap ? found : cap;
     float4 c0n = make_float4(0.f, 0.f, 0.f, 0.f), c0p = c0n;
     if (tid < nc) {
@@ -3384,7 +3433,7 @@ __global__ __launch_bounds__(BS, 2) void rollout_kernel(RolloutArgs r) {
     if (tid == 0 && r.ncon_traj) r.ncon_traj[(size_t)t * nw + w] = nc;
     if (tid == 0 && r.over_traj) r.over_traj[(size_t)t * nw + w] = found - nc;
     __syncthreads();
-    resolve_world<CONDIM, BS, ART>(ra, w, sq, sv, st, cn, cp, nc, c0n, c0p, mi0, reg, 0);
+    resolve_world<CONDIM, BS, ART>(ra, wc, sq, sv, st, cn, cp, nc, c0n, c0p, mi0, reg, 0);
     float *qo = r.q_traj + ((size_t)(t + 1) * nw + w) * nq, *vo = r.v_traj + ((size_t)(t + 1) * nw + w) * nv;
     for (int i = tid; i < nq; i += BS) qo[i] = sq[i];
     for (int i = tid; i < nv; i += BS) vo[i] = sv[i];
@@ -3503,10 +3552,14 @@ hipError_t launch_rollout_free(const RolloutArgs &a, size_t lds, int waves, hipS
 
 template <int CONDIM, bool ART>
 static hipError_t launch_rollout_b(const RolloutArgs &a, int block, size_t lds, hipStream_t s) {
+  if (ART && block == 64 && a.const_ofs > 0) {
+    hipLaunchKernelGGL((rollout_kernel<CONDIM, 64, ART, ART>), dim3(a.nworld), dim3(64), lds, s, a);
+    return hipGetLastError();
+  }
   switch (block) {
-    case 64: hipLaunchKernelGGL((rollout_kernel<CONDIM, 64, ART>), dim3(a.nworld), dim3(64), lds, s, a); break;
-    case 128: hipLaunchKernelGGL((rollout_kernel<CONDIM, 128, ART>), dim3(a.nworld), dim3(128), lds, s, a); break;
-    case 256: hipLaunchKernelGGL((rollout_kernel<CONDIM, 256, ART>), dim3(a.nworld), dim3(256), lds, s, a); break;
+    case 64: hipLaunchKernelGGL((rollout_kernel<CONDIM, 64, ART, false>), dim3(a.nworld), dim3(64), lds, s, a); break;
+    case 128: hipLaunchKernelGGL((rollout_kernel<CONDIM, 128, ART, false>), dim3(a.nworld), dim3(128), lds, s, a); break;
+    case 256: hipLaunchKernelGGL((rollout_kernel<CONDIM, 256, ART, false>), dim3(a.nworld), dim3(256), lds, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
