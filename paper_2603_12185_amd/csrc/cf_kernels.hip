@@ -1308,7 +1308,9 @@ __device__ __attribute__((always_inline)) inline void sphere_masks_mfma(const fl
 // caller's prefetch of slots[threadIdx.x]; `pre`, when given, the caller's
 // prefetch of geoms threadIdx.x and threadIdx.x + BS (each valid where below
 // ng).  Ends with a workgroup barrier.
-template <int BS, bool ART>
+// SPH: the ways of testing the sphere block that the kernel holds (0: both, by
+// the block's size; 1: slot by slot; 2: masks).
+template <int BS, bool ART, int SPH = 0>
 __device__ int collide_world(const CollideArgs &a, int w, const float *sq, float4 *reg, float4 *outn,
                              float4 *outp, int cap, uint32_t nxt, const GeomIn *pre = nullptr, int tid_in = -1) {
   constexpr int NW = BS / 64;
@@ -1557,7 +1559,7 @@ __device__ int collide_world(const CollideArgs &a, int w, const float *sq, float
   // are exact state values) and stored in order.  A pair is a contact when
   // |c_b - c_a|^2 < (r_a + r_b + margin)^2 (the same float32 value from either
   // end of the pair).
-  if (a.nsph > 0 && a.nsph <= kDirectSpheres) {
+  if (SPH != 2 && a.nsph > 0 && a.nsph <= kDirectSpheres) {
     // few pairs: one slot of the block per lane and pass, hits compacted in slot
     // order (their records at once when one pass covers the pairs, else from
     // the candidate list), without masks, their transposition and a row scan
@@ -1599,7 +1601,7 @@ __device__ int collide_world(const CollideArgs &a, int w, const float *sq, float
     }
     if (!one) __syncthreads();
     running += n;
-  } else if (a.nsph > 0) {
+  } else if (SPH != 1 && a.nsph > 0) {
     __shared__ int wsum[NW];
     const int g0 = a.sph0, S = a.nsph, nwd = (S + 63) >> 6;
     unsigned long long *rm = reinterpret_cast<unsigned long long *>(
@@ -2890,9 +2892,11 @@ __global__ __launch_bounds__(BS) void resolve_free_kernel(ResolveArgs a) {
 // float32 rounding (the compiler may fuse a multiply and an add differently in
 // the two compilations).
 // Four resident worlds per SIMD, as each phase's own kernel holds: condim
-// 1/3/4 need 95/111/123 VGPRs; condim 6, bounded to 128, spills 40 bytes.
-template <int CONDIM>
-__global__ __launch_bounds__(64, CONDIM == 6 ? 4 : 1) void step_free_kernel(CollideArgs ca, ResolveArgs ra) {
+// 1/3/4 need 105/113/125 VGPRs; condim 6, bounded to 128, spills 36 bytes.
+// Each way of testing the sphere block has its own kernel: with both in one, 64
+// spheres at condim 6 took 30.2 us instead of 28.8.
+template <int CONDIM, int SPH>
+__global__ __launch_bounds__(64, 4) void step_free_kernel(CollideArgs ca, ResolveArgs ra) {
   constexpr int BS = 64, K = 512 / BS;
   extern __shared__ float4 lds[];
   const int w = blockIdx.x, tid = threadIdx.x;
@@ -2920,7 +2924,7 @@ __global__ __launch_bounds__(64, CONDIM == 6 ? 4 : 1) void step_free_kernel(Coll
   rq.store(sq, qw, ca.nq);
   __syncthreads();
   const size_t cbase = (size_t)w * ca.ncon_max;
-  const int found = collide_world<BS, false>(ca, w, sq, lds + pad4(ca.nq) / 4, ca.cnp + cbase, ca.cpos + cbase,
+  const int found = collide_world<BS, false, SPH>(ca, w, sq, lds + pad4(ca.nq) / 4, ca.cnp + cbase, ca.cpos + cbase,
                                              ca.ncon_max, nxt, pre);
   const int nc = found < ca.ncon_max ? found : ca.ncon_max;
   if (tid == 0) {
@@ -2952,16 +2956,23 @@ __global__ __launch_bounds__(64, CONDIM == 6 ? 4 : 1) void step_free_kernel(Coll
   }
 }
 
-hipError_t launch_step_free(const CollideArgs &ca, const ResolveArgs &ra, int nworld, size_t lds, hipStream_t s) {
-  if (ra.nsub > 0 || ra.mlp || ra.act || ra.nb > 64 || ra.nb < 1) return hipErrorInvalidValue;
+template <int SPH>
+static hipError_t launch_step_free_s(const CollideArgs &ca, const ResolveArgs &ra, int nworld, size_t lds,
+                                     hipStream_t s) {
   switch (ra.condim) {
-    case 1: hipLaunchKernelGGL((step_free_kernel<1>), dim3(nworld), dim3(64), lds, s, ca, ra); break;
-    case 3: hipLaunchKernelGGL((step_free_kernel<3>), dim3(nworld), dim3(64), lds, s, ca, ra); break;
-    case 4: hipLaunchKernelGGL((step_free_kernel<4>), dim3(nworld), dim3(64), lds, s, ca, ra); break;
-    case 6: hipLaunchKernelGGL((step_free_kernel<6>), dim3(nworld), dim3(64), lds, s, ca, ra); break;
+    case 1: hipLaunchKernelGGL((step_free_kernel<1, SPH>), dim3(nworld), dim3(64), lds, s, ca, ra); break;
+    case 3: hipLaunchKernelGGL((step_free_kernel<3, SPH>), dim3(nworld), dim3(64), lds, s, ca, ra); break;
+    case 4: hipLaunchKernelGGL((step_free_kernel<4, SPH>), dim3(nworld), dim3(64), lds, s, ca, ra); break;
+    case 6: hipLaunchKernelGGL((step_free_kernel<6, SPH>), dim3(nworld), dim3(64), lds, s, ca, ra); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+hipError_t launch_step_free(const CollideArgs &ca, const ResolveArgs &ra, int nworld, size_t lds, hipStream_t s) {
+  if (ra.nsub > 0 || ra.mlp || ra.act || ra.nb > 64 || ra.nb < 1) return hipErrorInvalidValue;
+  return ca.nsph <= kDirectSpheres ? launch_step_free_s<1>(ca, ra, nworld, lds, s)
+                                   : launch_step_free_s<2>(ca, ra, nworld, lds, s);
 }
 
 // One step of a world with articulated subtrees in one one-wave workgroup:
@@ -3363,7 +3374,7 @@ static_assert(sizeof(BodyC) % sizeof(float4) == 0 && sizeof(SubTree) == 10 * siz
 // constants from L2 and passed the subtrees' frames through it.
 // They are copied to LDS once and the narrow phase and the resolution read
 // them, and the frames, there (the same arithmetic, bit for bit): a batch of
-// 2048 hands and 20 steps FIGURE.
+// 2048 hands and 20 steps takes 430 us in the kernel, 505 us before.
 template <int CONDIM, int BS, bool ART, bool LC>
 __global__ __launch_bounds__(BS, 2) void rollout_kernel(RolloutArgs r) {
   extern __shared__ float4 lds[];
