@@ -412,9 +412,9 @@ cf_status cf_model_create(const cf_model_desc *d, cf_model **out) {
       }
     }
     // The block's hit masks come from an MFMA Gram matrix when it holds at most
-    // 64 spheres on pairwise different bodies (so every pair is a slot) and the
+    // 128 spheres on pairwise different bodies (so every pair is a slot) and the
     // margin is not negative (then r_i + r_j + margin > 0 for every pair).
-    if (m->nsph > 0 && m->nsph <= 64 && m->p.margin >= 0.f) {
+    if (m->nsph > 0 && m->nsph <= 128 && m->p.margin >= 0.f) {
       std::vector<int> bodies;
       for (int g = m->sph0; g < ng; ++g) bodies.push_back(d->geom_body[g]);
       std::sort(bodies.begin(), bodies.end());

@@ -101,7 +101,7 @@ struct CollideArgs {
   int nslot_pre;                // slots tested one by one (all of them when nsph = 0)
   int sph0, nsph;               // sphere block: geoms [sph0, sph0 + nsph), pairs tested row-wise
   int npl;                      // > 0: geoms [0, npl) are static planes whose slots are their rows against the block
-  int sph_mfma;                 // 1: block of <= 64 spheres on pairwise different bodies, margin >= 0 (MFMA masks)
+  int sph_mfma;                 // 1: block of <= 128 spheres on pairwise different bodies, margin >= 0 (MFMA masks)
   const JointK<double> *jk;     // [nb] joint constants (articulated models)
   float4 *frames;               // [nw][nb][5] frames of small-subtree bodies (origin, joint axis,
                                 // rotation rows) for the resolution, or null

@@ -1136,16 +1136,19 @@ __device__ inline bool sphere_pair_hit(float4 Gi, float4 Gj, float margin) {
 // n = (c_b - c_a)/|c_b - c_a| (+z for coincident centres), phi = |c_b - c_a| -
 // r_a - r_b, point c_a + (r_a + phi/2) n, the slot word in the last lane.  The
 // distance and the normal come from one hardware reciprocal square root.
+// Every multiply-add is written as fmaf and nothing else is fused, so that every
+// kernel and path writes the same bits.
 __device__ inline void sphere_pair_record(float4 A, float4 B, uint32_t sl, float4 &cn, float4 &cp) {
-  const V3 d = v3(B.x - A.x, B.y - A.y, B.z - A.z);
-  const float d2 = dot(d, d);
+#pragma clang fp contract(off)
+  const float dx = B.x - A.x, dy = B.y - A.y, dz = B.z - A.z;
+  const float d2 = fmaf(dz, dz, fmaf(dx, dx, dy * dy));
   const bool apart = d2 >= 1e-24f;
   const float inv = apart ? __builtin_amdgcn_rsqf(d2) : 0.f;
-  const V3 n = apart ? inv * d : v3(0.f, 0.f, 1.f);
-  const float phi = d2 * inv - A.w - B.w;
-  const float k = A.w + 0.5f * phi;
-  cn = make_float4(n.x, n.y, n.z, phi);
-  cp = make_float4(A.x + k * n.x, A.y + k * n.y, A.z + k * n.z, __uint_as_float(sl));
+  const float nx = apart ? inv * dx : 0.f, ny = apart ? inv * dy : 0.f, nz = apart ? inv * dz : 1.f;
+  const float phi = fmaf(d2, inv, -A.w) - B.w;
+  const float k = fmaf(0.5f, phi, A.w);
+  cn = make_float4(nx, ny, nz, phi);
+  cp = make_float4(fmaf(k, nx, A.x), fmaf(k, ny, A.y), fmaf(k, nz, A.z), __uint_as_float(sl));
 }
 
 // Sphere blocks of up to this many spheres test their pairs slot by slot: a step
@@ -1192,114 +1195,143 @@ __device__ inline void sphere_masks(const float4 *Gs, const int *gbd, int g0, in
   }
 }
 
-// Hit masks of a sphere block of S <= 64 spheres on pairwise different
+// Hit masks of a sphere block of S <= 64 NW spheres on pairwise different
 // bodies (at most one static) with margin >= 0, from a Gram matrix on bf16
-// MFMA, one wave.  With centres c taken relative to the block's mean and
-// rho = r + margin / 2, the test quantity g_ij = |c_i - c_j|^2 - (rho_i +
-// rho_j)^2 is the product a_i . b_j of the 6-vectors a = (x, y, z, rho, s, 1)
-// and b = (-2x, -2y, -2z, -2rho, 1, s), s = |c|^2 - rho^2.  Each float32
-// component is split into bf16 parts, a = ah + al (+ a rest below 2^-18 |a|),
-// and a . b is taken as ah . bh + ah . bl + al . bh: 18 exact bf16 products
-// summed in float32, one v_mfma_f32_16x16x32_bf16 per 16 x 16 tile (K groups
-// of eight: 0 ah.bh, 1 ah.bl, 2 al.bh, 3 zero), ten tiles for the upper
-// triangle of 64 spheres.  Every product is at most M = max(|c|^2 + rho^2)
-// in magnitude (their sum at most 4 M), so the dropped parts and the float32
-// sums put g within 6e-5 M of the float32 test of sphere_pair_hit: outside
-// the band |g| <= eps = M 2^-13 the sign of g is that test's answer, and the
-// pairs inside it are decided by sphere_pair_hit itself.  The masks are
-// therefore the ones sphere_masks builds.  The tiles are formed transposed,
-// so lane l holds row i = 16 I + l % 16 at columns 16 J + 4 (l / 16) + r and
-// sets its own bits; the four lanes of a row OR their parts at the end.
-// `ab`: 4 x 64 x 16 bytes of LDS scratch.
-__device__ __attribute__((always_inline)) inline void sphere_masks_mfma(const float4 *Gs, int g0, int S,
+// MFMA, by a workgroup of NW (1 or 2) waves.  With centres c taken relative to
+// a mean of the block and rho = r + margin / 2, the test quantity g_ij = |c_i -
+// c_j|^2 - (rho_i + rho_j)^2 is the product b_i . a_j of the 6-vectors a = (x, y,
+// z, rho, s, 1) and b = (-2x, -2y, -2z, -2rho, 1, s), s = |c|^2 - rho^2.  Each
+// float32 component is split into bf16 parts, a = ah + al (+ a rest below 2^-18
+// |a|), and b . a is taken as bh . ah + bl . ah + bh . al: 18 exact bf16
+// products summed in float32, one v_mfma_f32_16x16x32_bf16 per 16 x 16 tile (K
+// groups of eight: 0 bh.ah, 1 bl.ah, 2 bh.al, 3 zero), 10 tiles for the upper
+// triangle of 64 spheres, 36 for 128 (row blocks 0 3 4 7 in the first wave, 1 2
+// 5 6 in the second).  Only a's parts are stored; b's are a's with the first
+// four components times -2 (sign and exponent of the bf16 words; a zero becomes
+// 2^-126) and the last two exchanged, formed once per row block.  Every product
+// is at most M = max(|c|^2 + rho^2) in magnitude (their sum at most 4 M), so the
+// dropped parts and the float32 sums put g within 6e-5 M of the float32 test of
+// sphere_pair_hit: outside the band |g| <= eps = M 2^-13 the sign of g is that
+// test's answer, and the pairs inside it are decided by sphere_pair_hit itself.
+// The masks are therefore the ones sphere_masks builds.  The tiles are formed
+// transposed, so lane l holds row i = 16 I + l % 16 at columns 16 J + 4 (l / 16)
+// + r and sets its own bits; the four lanes of a row OR their parts at the end.
+// Bound by vector issue (four to six resident waves per SIMD), so a tile is kept
+// at about 16 instructions: the four answers are the sign bits of g + eps,
+// shifted in by v_alignbit, and the band is one minimum of magnitudes.  A step of
+// 4096 piles of 128 spheres takes 76.1 us, 84.0 with the lane-by-lane test; of 64
+// spheres 26.4 us, 26.8 with tiles of about 35 instructions.
+// Returns false, with nothing written, when a sphere is not finite (the caller
+// then tests lane by lane: only that sphere's own pairs are no contacts).
+// `ab`: NW x 2 x 64 x 16 bytes of LDS scratch.
+template <int NW>
+__device__ __attribute__((always_inline)) inline bool sphere_masks_mfma(const float4 *Gs, int g0, int S,
                                                                         float margin, unsigned long long *rm,
                                                                         void *ab) {
   typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
   typedef float f32x4 __attribute__((ext_vector_type(4)));
-  const int l = threadIdx.x;  // the workgroup is one wave
-  const bool real = l < S;
-  const float4 G = real ? Gs[g0 + l] : make_float4(0.f, 0.f, 0.f, 0.f);
-  const float invS = 1.0f / (float)S;
-  const float cx = wave_last(wave_incl_sum(real ? G.x : 0.f)) * invS,
-              cy = wave_last(wave_incl_sum(real ? G.y : 0.f)) * invS,
-              cz = wave_last(wave_incl_sum(real ? G.z : 0.f)) * invS;
-  const float x = G.x - cx, y = G.y - cy, z = G.z - cz;
-  const float rho = G.w + 0.5f * margin;
-  const float c2 = fmaf(z, z, fmaf(y, y, x * x)), r2 = rho * rho;
-  const float M = wave_last(wave_incl_max(real ? c2 + r2 : 0.f));
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  const int l = threadIdx.x & 63, wv = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // the wave's spheres; with two waves also the other half's sizes, so that both
+  // waves use the same centre (the first 64 spheres' mean) and bound M
+  float4 G[NW];
+  bool real[NW];
+  float ext = 0.f, any = 0.f;
+#pragma unroll
+  for (int k = 0; k < NW; ++k) {
+    real[k] = 64 * k + l < S;
+    G[k] = Gs[g0 + (real[k] ? 64 * k + l : 0)];
+    ext = fmaxf(fmaxf(fmaxf(ext, fabsf(G[k].x)), fmaxf(fabsf(G[k].y), fabsf(G[k].z))), fabsf(G[k].w));
+    any += G[k].x + G[k].y + G[k].z + G[k].w;  // NaN where one is (fmaxf drops it)
+  }
+  if (__builtin_amdgcn_ballot_w64(!(ext < 1e15f) || any != any)) return false;
+  const float invS = 1.0f / (float)(S < 64 ? S : 64);
+  const float cx = wave_last(wave_incl_sum(real[0] ? G[0].x : 0.f)) * invS,
+              cy = wave_last(wave_incl_sum(real[0] ? G[0].y : 0.f)) * invS,
+              cz = wave_last(wave_incl_sum(real[0] ? G[0].z : 0.f)) * invS;
+  float x = 0.f, y = 0.f, z = 0.f, rho = 0.f, c2 = 0.f, r2 = 0.f, m = 0.f;
+  bool mine = false;
+#pragma unroll
+  for (int k = NW - 1; k >= 0; --k) {
+    const float xk = G[k].x - cx, yk = G[k].y - cy, zk = G[k].z - cz, rk = G[k].w + 0.5f * margin;
+    const float ck = fmaf(zk, zk, fmaf(yk, yk, xk * xk)), qk = rk * rk;
+    m = fmaxf(m, real[k] ? ck + qk : 0.f);
+    if (NW == 1 || wv == k) {
+      x = xk; y = yk; z = zk; rho = rk; c2 = ck; r2 = qk;
+      mine = real[k];
+    }
+  }
+  const float M = wave_last(wave_incl_max(m));
   const float eps = M * (1.0f / 8192.0f);
   // padding rows and columns sit at g >= 4 M + 1 > eps from everything
-  const float sa = real ? c2 - r2 : 4.0f * M + 1.0f;
-  const float av[6] = {real ? x : 0.f, real ? y : 0.f, real ? z : 0.f, real ? rho : 0.f, sa, 1.f};
-  const float bv[6] = {-2.f * av[0], -2.f * av[1], -2.f * av[2], -2.f * av[3], 1.f, sa};
-  bf16x8 ah, al, bh, bl;
+  const float av[6] = {mine ? x : 0.f, mine ? y : 0.f, mine ? z : 0.f, mine ? rho : 0.f,
+                       mine ? c2 - r2 : 4.0f * M + 1.0f, 1.f};
+  bf16x8 ah, al;
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
-    const float a = k < 6 ? av[k] : 0.f, b = k < 6 ? bv[k] : 0.f;
+    const float a = k < 6 ? av[k] : 0.f;
     ah[k] = (__bf16)a;
     al[k] = (__bf16)(a - (float)ah[k]);
-    bh[k] = (__bf16)b;
-    bl[k] = (__bf16)(b - (float)bh[k]);
   }
-  bf16x8 *tab = reinterpret_cast<bf16x8 *>(ab);  // [AH | AL | BH | BL][64]
-  tab[l] = ah;
-  tab[64 + l] = al;
-  tab[128 + l] = bh;
-  tab[192 + l] = bl;
+  bf16x8 *tab = reinterpret_cast<bf16x8 *>(ab);  // [AH | AL][64 NW]
+  tab[64 * wv + l] = ah;
+  tab[64 * NW + 64 * wv + l] = al;
   __syncthreads();
   const int c = l & 15, kg = l >> 4;
-  // K group of this lane: the row operand (a) is ah, ah, al, 0 and the column
-  // operand (b) bh, bl, bh, 0 for groups 0..3
-  const bf16x8 zero8 = {};
-  const bf16x8 *arow = tab + (kg == 2 ? 64 : 0), *bcol = tab + (kg == 1 ? 192 : 128);
+  // K group of this lane: rows (b) bh, bl, bh, 0 and columns (a) ah, ah, al, - for groups 0..3
+  const bf16x8 *brow = tab + (kg == 1 ? 64 * NW : 0), *acol = tab + (kg == 2 ? 64 * NW : 0);
+  const uint32_t live = kg < 3 ? 0xffffffffu : 0u;
+  // columns of a diagonal tile above the lane's row
+  const uint32_t diag = c < 4 * kg ? 15u : (15u << (c - 4 * kg < 3 ? c - 4 * kg + 1 : 4)) & 15u;
   const int nt = (S + 15) >> 4;
-  // the lane's bits of row 16 I + c (columns 16 J + 4 kg + r), per row block I
-  uint32_t part[4][4] = {};
-  uint32_t bit[4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) bit[r] = 1u << (4 * kg + r);
-#pragma unroll
-  for (int I = 0; I < 4; ++I) {
+  for (int ii = 0; ii < 4; ++ii) {
+    const int I = NW == 1 ? ii : 2 * ii + (wv ^ (ii & 1));
     if (I >= nt) break;
-    const bf16x8 bop = kg < 3 ? arow[16 * I + c] : zero8;  // rows i of this block (the product's N side)
+    u32x4 row = __builtin_bit_cast(u32x4, brow[16 * I + c]);
+    row[0] = ((row[0] ^ 0x80008000u) + 0x00800080u) & live;
+    row[1] = ((row[1] ^ 0x80008000u) + 0x00800080u) & live;
+    row[2] = __builtin_amdgcn_alignbit(row[2], row[2], 16) & live;
+    row[3] = 0u;
+    const bf16x8 bop = __builtin_bit_cast(bf16x8, row);
+    uint32_t word[2 * NW];
 #pragma unroll
-    for (int J = 0; J < 4; ++J) {
+    for (int k = 0; k < 2 * NW; ++k) word[k] = 0u;
+#pragma unroll
+    for (int J = 0; J < 4 * NW; ++J) {
       if (J < I || J >= nt) continue;
-      const bf16x8 aop = kg < 3 ? bcol[16 * J + c] : zero8;  // columns j (the product's M side)
       f32x4 g = {0.f, 0.f, 0.f, 0.f};
-      g = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aop, bop, g, 0, 0, 0);
-      // lane l: g[r] = g_ij, i = 16 I + c, j = 16 J + 4 kg + r; a diagonal
-      // tile keeps the columns above the row
-      bool amb = false;
+      g = __builtin_amdgcn_mfma_f32_16x16x32_bf16(acol[16 * J + c], bop, g, 0, 0, 0);
+      // lane l: g[r] = g_ij, i = 16 I + c, j = 16 J + 4 kg + r; bit r of `hit`: g[r] + eps < 0
+      uint32_t hit = 0u;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const bool above = I < J || 4 * kg + r > c;
-        part[I][J] |= (above && g[r] < -eps) ? bit[r] : 0u;
-        amb |= above && fabsf(g[r]) <= eps;
-      }
-      if (__builtin_amdgcn_ballot_w64(amb)) {  // pairs in the band (rare): the float32 test itself
-        if (amb) {
-          const float4 Gi = Gs[g0 + 16 * I + c];
+      for (int r = 3; r >= 0; --r) hit = __builtin_amdgcn_alignbit(hit, __float_as_uint(g[r] + eps), 31);
+      const float least = fminf(fminf(fabsf(g[0]), fabsf(g[1])), fminf(fabsf(g[2]), fabsf(g[3])));
+      if (__builtin_amdgcn_ballot_w64(least <= eps)) {  // pairs in the band (rare): the float32 test itself
+        if (least <= eps) {
+          const float4 Gi = Gs[g0 + (16 * I + c < S ? 16 * I + c : 0)];
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            const bool above = I < J || 4 * kg + r > c;
-            if (above && fabsf(g[r]) <= eps && sphere_pair_hit(Gi, Gs[g0 + 16 * J + 4 * kg + r], margin))
-              part[I][J] |= bit[r];
+            const int j = 16 * J + 4 * kg + r;
+            if (fabsf(g[r]) <= eps && j < S && sphere_pair_hit(Gi, Gs[g0 + j], margin)) hit |= 1u << r;
           }
         }
       }
+      if (I == J) hit &= diag;
+      word[J >> 1] |= hit << (4 * kg + 16 * (J & 1));
+    }
+    // the four lanes of a row (equal l % 16) OR their parts into its mask words
+    // (zero on entry; integer OR is order-free)
+    if (16 * I + c < S) {
+#pragma unroll
+      for (int k = 0; k < NW; ++k) {
+        const unsigned long long v = (unsigned long long)word[2 * k] | ((unsigned long long)word[2 * k + 1] << 32);
+        if (v) atomicOr(rm + NW * (16 * I + c) + k, v);
+      }
     }
   }
-  // the four lanes of a row (equal l % 16) OR their parts into its mask
-  // (zero on entry; integer OR is order-free)
-#pragma unroll
-  for (int I = 0; I < 4; ++I) {
-    if (I >= nt) break;
-    const unsigned long long m = (unsigned long long)(part[I][0] | (part[I][1] << 16)) |
-                                 ((unsigned long long)(part[I][2] | (part[I][3] << 16)) << 32);
-    if (m && 16 * I + c < S) atomicOr(rm + 16 * I + c, m);
-  }
   __syncthreads();
+  return true;
 }
 
 // Narrow phase of world w from its q row `sq` (LDS).  Writes the first `cap`
@@ -1608,8 +1640,11 @@ __device__ int collide_world(const CollideArgs &a, int w, const float *sq, float
         a.nsub > 0 ? reinterpret_cast<char *>(brot + 12 * a.nb) : reinterpret_cast<char *>(borg));
     for (int x = tid; x < S * nwd; x += BS) rm[x] = 0ull;
     __syncthreads();
-    if (BS == 64 && a.sph_mfma) {
-      sphere_masks_mfma(Gs, g0, S, a.margin, rm, cand);
+    bool done = false;  // (uniform over the workgroup)
+    if (BS == 64 && a.sph_mfma && S <= 64) done = sphere_masks_mfma<1>(Gs, g0, S, a.margin, rm, cand);
+    if (BS == 128 && a.sph_mfma && S > 64 && S <= 128) done = sphere_masks_mfma<2>(Gs, g0, S, a.margin, rm, cand);
+    if (done) {
+      // masks written
     } else if (S <= 64) {
       sphere_masks<BS, 1>(Gs, gbd, g0, S, a.margin, rm);
     } else if (S <= 128) {
