@@ -593,13 +593,14 @@ static bool rollout_free(const cf_model *m) {
   return m->lds_rollout_free > 0 && m->lds_rollout_free <= kLdsLimit && !m->d_act && !m->mlp;
 }
 
-// Worlds of at most 64 free bodies (no actuators, no learned gains) at the
-// one-wave launch shapes: cf_step runs the narrow phase and the resolution of
+// Worlds of at most 128 free bodies (no actuators, no learned gains) at the
+// launch shapes of one body per lane (one wave, two above 64 bodies): cf_step runs the narrow phase and the resolution of
 // each world in one kernel (not while kernel timing is on, which times the two
 // kernels apart).
 static bool step_fused(const cf_model *m) {
-  return !m->prof && !m->mlp && !m->d_act && m->nsub == 0 && m->nb >= 1 && m->nb <= 64 &&
-         m->block_collide == 64 && m->block_resolve == 64 &&
+  const int one = m->nb > 64 ? 128 : 64;  // the smallest workgroup that holds every body
+  return !m->prof && !m->mlp && !m->d_act && m->nsub == 0 && m->nb >= 1 && m->nb <= 128 &&
+         m->block_collide == one && m->block_resolve == one &&
          std::max(m->lds_collide, m->lds_resolve_free) <= kLdsLimit;
 }
 
