@@ -61,6 +61,8 @@ struct cf_model {
   float4 *d_bmi = nullptr, *d_gdat = nullptr, *d_gpos = nullptr, *d_gquat = nullptr;
   float *d_gmu = nullptr;  // [nworld][ngeom] tangential friction alone
   cf::JointK<double> *d_jk64 = nullptr;  // [nb] joint constants (narrow phase kinematics)
+  cf::PlanePose *d_planes = nullptr;     // [nworld or 1][npl] poses of the plane rows' planes
+  int planes_ws = 0;
   float4 *d_frames = nullptr;  // [nworld][nb][5] small-subtree frames, narrow phase -> resolution
   float2 *d_gfr2 = nullptr;
   int gpos_ws = 0, gquat_ws = 0;
@@ -140,7 +142,7 @@ void free_model(cf_model *m) {
   (void)hipFree(m->d_mlp_img);
   (void)hipFree(m->d_body); (void)hipFree(m->d_sub); (void)hipFree(m->d_bmi); (void)hipFree(m->d_gdat);
   (void)hipFree(m->d_gpos); (void)hipFree(m->d_gquat); (void)hipFree(m->d_gfr2); (void)hipFree(m->d_gmu);
-  (void)hipFree(m->d_jk64); (void)hipFree(m->d_frames);
+  (void)hipFree(m->d_jk64); (void)hipFree(m->d_frames); (void)hipFree(m->d_planes);
   (void)hipFree(m->d_cnp); (void)hipFree(m->d_cpos); (void)hipFree(m->d_ncon); (void)hipFree(m->d_over);
   for (auto &s : m->events)
     for (auto e : s.e) (void)hipEventDestroy(e);
@@ -527,6 +529,14 @@ cf_status cf_model_create(const cf_model_desc *d, cf_model **out) {
   chk(upload(&m->d_gpos, gpos));
   chk(upload(&m->d_gquat, gquat));
   if (m->condim >= 4) chk(upload(&m->d_gfr2, gfr2));
+  if (m->npl > 0) {
+    const int count = (m->gpos_ws || m->gquat_ws) ? nw : 1;
+    m->planes_ws = count > 1 ? m->npl : 0;
+    chk(hipMalloc((void **)&m->d_planes, sizeof(cf::PlanePose) * (size_t)count * m->npl));
+    if (e == hipSuccess)
+      chk(cf::launch_plane_poses(m->d_gpos, m->gpos_ws, m->d_gquat, m->gquat_ws, m->npl, count, m->d_planes, nullptr));
+    if (e == hipSuccess) chk(hipStreamSynchronize(nullptr));  // read by launches on other streams
+  }
   const size_t ncap = (size_t)nw * (m->ncon_max > 0 ? m->ncon_max : 1);
   chk(hipMalloc((void **)&m->d_cnp, sizeof(float4) * ncap));
   chk(hipMalloc((void **)&m->d_cpos, sizeof(float4) * ncap));
@@ -571,6 +581,7 @@ static cf::CollideArgs collide_args(const cf_model *m) {
   ca.nq = m->nq; ca.nb = m->nb; ca.ng = m->ng; ca.nslot = m->nslot; ca.ncon_max = m->ncon_max;
   ca.gpos_ws = m->gpos_ws; ca.gquat_ws = m->gquat_ws; ca.margin = m->p.margin;
   ca.nslot_pre = m->nslot_pre; ca.sph0 = m->sph0; ca.nsph = m->nsph; ca.npl = m->npl; ca.sph_mfma = m->sph_mfma;
+  ca.planes = m->d_planes; ca.planes_ws = m->planes_ws;
   return ca;
 }
 

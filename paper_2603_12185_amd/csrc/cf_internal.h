@@ -82,6 +82,13 @@ struct Params {
   float mlp_margin;                     // fallback margin of the learned gains (m)
 };
 
+// World pose of a static plane (local z is its normal), a model constant written
+// once by launch_plane_poses.
+struct PlanePose {
+  float n[4], p[4];    // float32 normal and position
+  double nd[4], pd[4]; // float64 normal and position
+};
+
 // Collision kernel: one workgroup per world.
 struct CollideArgs {
   const float *q;               // [nw][nq]
@@ -101,6 +108,8 @@ struct CollideArgs {
   int nslot_pre;                // slots tested one by one (all of them when nsph = 0)
   int sph0, nsph;               // sphere block: geoms [sph0, sph0 + nsph), pairs tested row-wise
   int npl;                      // > 0: geoms [0, npl) are static planes whose slots are their rows against the block
+  const PlanePose *planes;      // npl > 0: the planes' poses, [nw|1][npl]
+  int planes_ws;                // their world stride in planes (0 = shared by all worlds)
   int sph_mfma;                 // 1: block of <= 128 spheres on pairwise different bodies, margin >= 0 (MFMA masks)
   const JointK<double> *jk;     // [nb] joint constants (articulated models)
   float4 *frames;               // [nw][nb][5] frames of small-subtree bodies (origin, joint axis,
@@ -191,6 +200,11 @@ size_t adjoint_free_lds_bytes(int nq, int nb, int ng, int norient, int nsph, int
 hipError_t launch_adjoint_free(AdjointArgs a, size_t lds, hipStream_t s);
 // x += y, n floats.
 hipError_t launch_add_rows(float *x, const float *y, size_t n, hipStream_t s);
+
+// Poses of the planes (geoms 0 .. npl - 1) of `count` geom tables from their
+// offsets and orientations (world strides in geoms, 0 = shared).
+hipError_t launch_plane_poses(const float4 *gpos, int gpos_ws, const float4 *gquat, int gquat_ws, int npl, int count,
+                              PlanePose *out, hipStream_t s);
 
 size_t collide_lds_bytes(int nq, int nb, int ng, int norient, int nsub, int nsph);
 size_t rollout_lds_bytes(int nq, int nv, int nb, int ng, int norient, int nsub, int nsph, int art_floats, int cap);
