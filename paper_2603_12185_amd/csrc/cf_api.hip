@@ -873,20 +873,26 @@ cf_status cf_rollout(cf_model *m, void *stream, int32_t T, const float *q0, cons
     return set_err(CF_E_INVALID_ARG, "state buffers must be 16-byte aligned");
   const size_t sq = (size_t)m->nw * m->nq, sv = (size_t)m->nw * m->nv;
   hipStream_t s = (hipStream_t)stream;
-  if (q0 != q_traj && hipMemcpyAsync(q_traj, q0, sizeof(float) * sq, hipMemcpyDeviceToDevice, s) != hipSuccess)
-    return set_err(CF_E_DEVICE, "hipMemcpyAsync failed");
-  if (v0 != v_traj && hipMemcpyAsync(v_traj, v0, sizeof(float) * sv, hipMemcpyDeviceToDevice, s) != hipSuccess)
-    return set_err(CF_E_DEVICE, "hipMemcpyAsync failed");
+  // Row 0 is the initial state.  The persistent kernels write it as they read
+  // the state (a copy each costs a launch's gap) unless that state lies in what
+  // they write: a world could then find its row overwritten by another one's.
+  auto apart = [](const float *a, size_t na, const float *b, size_t nb) { return a + na <= b || b + nb <= a; };
+  const size_t tq = (size_t)(T + 1) * sq, tv = (size_t)(T + 1) * sv;
+  const bool row0 = T > 0 && rollout_fused(m) && apart(q0, sq, q_traj, tq) && apart(q0, sq, v_traj, tv) &&
+                    apart(v0, sv, q_traj, tq) && apart(v0, sv, v_traj, tv);
+  if (!row0) {
+    if (q0 != q_traj && hipMemcpyAsync(q_traj, q0, sizeof(float) * sq, hipMemcpyDeviceToDevice, s) != hipSuccess)
+      return set_err(CF_E_DEVICE, "hipMemcpyAsync failed");
+    if (v0 != v_traj && hipMemcpyAsync(v_traj, v0, sizeof(float) * sv, hipMemcpyDeviceToDevice, s) != hipSuccess)
+      return set_err(CF_E_DEVICE, "hipMemcpyAsync failed");
+  }
   if (T == 0) return CF_OK;
   if (rollout_fused(m)) {
     cf::RolloutArgs r{};
     r.c = collide_args(m);
     r.s = resolve_args(m);
-    r.q0 = q_traj; r.v0 = v_traj; r.tau_seq = tau_seq; r.q_traj = q_traj; r.v_traj = v_traj;
+    r.q0 = row0 ? q0 : q_traj; r.v0 = row0 ? v0 : v_traj; r.row0 = row0; r.tau_seq = tau_seq; r.q_traj = q_traj; r.v_traj = v_traj;
     r.ncon_traj = ncon_traj; r.over_traj = overflow_traj; r.T = T; r.nworld = m->nw; r.cap = m->ncon_max;
-    // the free-body kernel sized for three resident waves per SIMD (twelve
-    // one-wave worlds per CU, no register spills) while the batch fits the
-    // device at that occupancy, else for four
     // one-wave worlds of articulated models keep their constants in LDS where
     // eight worlds (two waves per SIMD) still share a CU's 160 KB with them
     size_t lds = (m->lds_rollout + 15) / 16 * 16;
@@ -895,9 +901,23 @@ cf_status cf_rollout(cf_model *m, void *stream, int32_t T, const float *q0, cons
       r.const_ofs = (int)(lds / 16);
       lds += consts;
     }
-    hipError_t e = rollout_free(m)
-                       ? cf::launch_rollout_free(r, m->lds_rollout_free, m->nw <= 12 * m->ncu ? 3 : 4, s)
-                       : cf::launch_rollout(r, m->block_rollout, lds, s);
+    hipError_t e;
+    if (rollout_free(m)) {
+      // Up to four worlds per CU (one wave per SIMD) and up to eight (two) the
+      // kernel that holds state, constants and contact records on the chip,
+      // where every world's share of the CU's 160 KB of LDS holds its
+      // contacts (a step of 256 pushers, five bodies: 4.3 us, 5.0 without;
+      // 1500: 5.4, 6.2; of 1024 piles of 8 spheres: 5.1, 6.2; of 64 spheres at
+      // condim 6: 15.8, 16.0); else the other one, sized for three resident
+      // waves per SIMD (twelve worlds per CU, next to no register spills)
+      // while the batch fits the device at that occupancy, else for four.
+      const size_t held = cf::rollout_held_lds_bytes(m->nq, m->nb, m->ng, m->norient, m->nsph, m->ncon_max);
+      const int waves = m->nw <= 4 * m->ncu ? 1 : m->nw <= 8 * m->ncu ? 2 : m->nw <= 12 * m->ncu ? 3 : 4;
+      const bool hold = waves <= 2 && held <= kLdsLimit && held * ((m->nw + m->ncu - 1) / m->ncu) <= 160 * 1024;
+      e = cf::launch_rollout_free(r, hold ? held : m->lds_rollout_free, hold ? waves : std::max(waves, 3), s);
+    } else {
+      e = cf::launch_rollout(r, m->block_rollout, lds, s);
+    }
     if (e != hipSuccess) return set_err(CF_E_DEVICE, std::string("rollout launch: ") + hipGetErrorString(e));
     return CF_OK;
   }

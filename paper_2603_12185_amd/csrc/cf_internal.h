@@ -152,10 +152,11 @@ struct RolloutArgs {
   ResolveArgs s;                // q, v, tau, outputs, contact inputs and exports unused
   const float *q0, *v0;         // [nw][nq], [nw][nv]
   const float *tau_seq;         // [T][nw][nv] or null
-  float *q_traj, *v_traj;       // [T+1][nw][..]; row 0 written by the host
+  float *q_traj, *v_traj;       // [T+1][nw][..]
   int *ncon_traj;               // [T][nw] contacts kept per step, or null
   int *over_traj;               // [T][nw] contacts dropped beyond cap per step, or null
   int T, nworld, cap;           // cap: contacts held per world per step (= ncon_max)
+  int row0;                     // 1: also write row 0 of the trajectories (0: it is q0, v0 already)
   int const_ofs;                // > 0: float4 offset in LDS of the world's model constants (rollout_const_bytes)
 };
 
@@ -229,6 +230,8 @@ size_t resolve_learned_k32_lds_bytes(int nb, int ng);
 // (sixteen).
 bool rollout_free_fits(int nq, int nb);
 size_t rollout_free_lds_bytes(int nb, int ng, int norient, int nsph);
+size_t rollout_held_lds_bytes(int nq, int nb, int ng, int norient, int nsph, int cap);
+// waves 1, 2: rollout_held_kernel with `lds` = rollout_held_lds_bytes(), else rollout_free_kernel
 hipError_t launch_rollout_free(const RolloutArgs &a, size_t lds, int waves, hipStream_t s);
 hipError_t launch_resolve_learned(const ResolveArgs &a, int nworld, size_t lds, hipStream_t s);
 size_t mlp_image_k32_bytes();

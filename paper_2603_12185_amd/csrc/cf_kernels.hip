@@ -3465,6 +3465,10 @@ __global__ __launch_bounds__(BS, 2) void rollout_kernel(RolloutArgs r) {
     const float *qw = r.q0 + (size_t)w * nq, *vw = r.v0 + (size_t)w * nv;
     for (int i = tid; i < nq; i += BS) sq[i] = qw[i];
     for (int i = tid; i < nv; i += BS) sv[i] = vw[i];
+    if (r.row0) {
+      for (int i = tid; i < nq; i += BS) r.q_traj[(size_t)w * nq + i] = sq[i];
+      for (int i = tid; i < nv; i += BS) r.v_traj[(size_t)w * nv + i] = sv[i];
+    }
   }
   int wc = w;  // the world's index in the model constants
   if constexpr (LC) {
@@ -3567,7 +3571,13 @@ __global__ __launch_bounds__(64, WAVES) void rollout_free_kernel(RolloutArgs r) 
   const int nq = ra.nq, nv = ra.nv, nb = ra.nb, nw = r.nworld, cap = r.cap;
   const bool own = tid < nb;
   float *sq = reinterpret_cast<float *>(reinterpret_cast<char *>(lds) + collide_cand_offset(ca.ng, ca.norient));
-  for (int i = tid; i < nq; i += BS) sq[i] = r.q_traj[(size_t)w * nq + i];  // row 0 = the initial state
+  for (int i = tid; i < nq; i += BS) {
+    const float x = r.q0[(size_t)w * nq + i];
+    sq[i] = x;
+    if (r.row0) r.q_traj[(size_t)w * nq + i] = x;
+  }
+  if (r.row0)
+    for (int i = tid; i < nv; i += BS) r.v_traj[(size_t)w * nv + i] = r.v0[(size_t)w * nv + i];
   const uint32_t nxt = tid < ca.nslot_pre ? ca.slots[tid] : 0u;
   for (int t = 0; t < r.T; ++t) {
     // the world and lane index, opaque to the compiler in each step, so
@@ -3590,8 +3600,8 @@ __global__ __launch_bounds__(64, WAVES) void rollout_free_kernel(RolloutArgs r) 
     const float4 cn = ca.cnp[cbase + r0], cp = ca.cpos[cbase + r0];
     float qb[7], vb[6], tb[6];
     {
-      const float *qs = r.q_traj + ((size_t)t * nw + wt) * nq + 7 * bl;
-      const float *vs = r.v_traj + ((size_t)t * nw + wt) * nv + 6 * bl;
+      const float *qs = (t > 0 ? r.q_traj + ((size_t)t * nw + wt) * nq : r.q0 + (size_t)wt * nq) + 7 * bl;
+      const float *vs = (t > 0 ? r.v_traj + ((size_t)t * nw + wt) * nv : r.v0 + (size_t)wt * nv) + 6 * bl;
 #pragma unroll
       for (int i = 0; i < 7; ++i) qb[i] = qs[i];
 #pragma unroll
@@ -3621,6 +3631,96 @@ __global__ __launch_bounds__(64, WAVES) void rollout_free_kernel(RolloutArgs r) 
   }
 }
 
+// The same for a batch that leaves a SIMD one or two worlds: one wave's chain of
+// dependent work is all that bounds it, so nothing of a step waits for memory.
+// Contact records and the q row have LDS of their own, the lane's state and its
+// share of the model's constants stay in registers from step to step (WAVES = 1:
+// 512 of them, 2: 256), and the applied forces of the next step are loaded
+// during this one.  32 steps of 256 pushers: 138 us, 159 with rollout_free_kernel
+// and two copies.
+size_t rollout_held_lds_bytes(int nq, int nb, int ng, int norient, int nsph, int cap) {
+  return sizeof(float) * pad4(nq) + 2 * sizeof(float4) * (size_t)cap +
+         (rollout_free_lds_bytes(nb, ng, norient, nsph) + 15) / 16 * 16;
+}
+
+template <int CONDIM, int WAVES>
+__global__ __launch_bounds__(64, WAVES) void rollout_held_kernel(RolloutArgs r) {
+  constexpr int BS = 64;
+  extern __shared__ float4 lds[];
+  const CollideArgs &ca = r.c;
+  const ResolveArgs &ra = r.s;
+  const int w = blockIdx.x, tid = threadIdx.x;
+  const int nq = ra.nq, nv = ra.nv, nb = ra.nb, ng = ra.ng, nw = r.nworld, cap = r.cap;
+  const bool own = tid < nb;
+  const int bl = own ? tid : nb - 1, gl = ng > 0 ? ng - 1 : 0;
+  float4 *cnp = lds, *cpos = cnp + cap;
+  float *sq = reinterpret_cast<float *>(cpos + cap);
+  float4 *reg = cpos + cap + pad4(nq) / 4;
+  for (int i = tid; i < nq; i += BS) {
+    const float x = r.q0[(size_t)w * nq + i];
+    sq[i] = x;
+    if (r.row0) r.q_traj[(size_t)w * nq + i] = x;
+  }
+  const uint32_t nxt = ca.slots[tid < ca.nslot_pre ? tid : (ca.nslot_pre > 0 ? ca.nslot_pre - 1 : 0)];
+  GeomIn g0 = geom_in(ca, w, tid < ng ? tid : gl), g1 = geom_in(ca, w, tid + BS < ng ? tid + BS : gl);
+  const FreeGeomPre gpre = free_geom_prefetch<CONDIM, BS>(ra, w, tid);
+  const float4 mi = ra.bmi[(size_t)w * nb + bl];
+  float qb[7], vb[6], tb[6];
+#pragma unroll
+  for (int i = 0; i < 7; ++i) qb[i] = r.q0[(size_t)w * nq + 7 * bl + i];
+#pragma unroll
+  for (int i = 0; i < 6; ++i) vb[i] = r.v0[(size_t)w * nv + 6 * bl + i];
+#pragma unroll
+  for (int i = 0; i < 6; ++i) tb[i] = r.tau_seq ? r.tau_seq[(size_t)w * nv + 6 * bl + i] : 0.f;
+  if (r.row0 && own)
+#pragma unroll
+    for (int i = 0; i < 6; ++i) r.v_traj[(size_t)w * nv + 6 * tid + i] = vb[i];
+  for (int t = 0; t < r.T; ++t) {
+    if (WAVES == 2)  // opaque in each step: the float64 rotations formed from them are not held across the steps
+      asm volatile("" : "+v"(g0.gq.x), "+v"(g0.gq.y), "+v"(g0.gq.z), "+v"(g0.gq.w), "+v"(g1.gq.x), "+v"(g1.gq.y),
+                   "+v"(g1.gq.z), "+v"(g1.gq.w));
+    const GeomIn pre[2] = {g0, g1};
+    float tn[6];
+    const size_t tr = (size_t)(t + 1 < r.T ? t + 1 : t) * nw + w;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) tn[i] = r.tau_seq ? r.tau_seq[tr * nv + 6 * bl + i] : 0.f;
+    __syncthreads();  // the q row is complete
+    const int found = collide_world<BS, false>(ca, w, sq, reg, cnp, cpos, cap, nxt, pre);
+    const int nc = found < cap ? found : cap;
+    if (tid == 0 && r.ncon_traj) r.ncon_traj[(size_t)t * nw + w] = nc;
+    if (tid == 0 && r.over_traj) r.over_traj[(size_t)t * nw + w] = found - nc;
+    const int r0 = tid < nc ? tid : (nc > 0 ? nc - 1 : 0);
+    __syncthreads();
+    const float4 cn = cnp[r0], cp = cpos[r0];
+    float qo[7], vo[6];
+    resolve_free_world<CONDIM, BS>(ra, w, qb, vb, tb, mi, nc, cn, cp, cnp, cpos, 0, reg, qo, vo, tid, &gpre);
+    if (own) {
+      float *qd = r.q_traj + ((size_t)(t + 1) * nw + w) * nq + 7 * tid;
+      float *vd = r.v_traj + ((size_t)(t + 1) * nw + w) * nv + 6 * tid;
+#pragma unroll
+      for (int i = 0; i < 7; ++i) {
+        qd[i] = sq[7 * tid + i] = qb[i] = qo[i];
+      }
+#pragma unroll
+      for (int i = 0; i < 6; ++i) vd[i] = vb[i] = vo[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 6; ++i) tb[i] = tn[i];
+  }
+}
+
+template <int WAVES>
+static hipError_t launch_rollout_held_w(const RolloutArgs &a, size_t lds, hipStream_t s) {
+  switch (a.s.condim) {
+    case 1: hipLaunchKernelGGL((rollout_held_kernel<1, WAVES>), dim3(a.nworld), dim3(64), lds, s, a); break;
+    case 3: hipLaunchKernelGGL((rollout_held_kernel<3, WAVES>), dim3(a.nworld), dim3(64), lds, s, a); break;
+    case 4: hipLaunchKernelGGL((rollout_held_kernel<4, WAVES>), dim3(a.nworld), dim3(64), lds, s, a); break;
+    case 6: hipLaunchKernelGGL((rollout_held_kernel<6, WAVES>), dim3(a.nworld), dim3(64), lds, s, a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 template <int WAVES>
 static hipError_t launch_rollout_free_w(const RolloutArgs &a, size_t lds, hipStream_t s) {
   switch (a.s.condim) {
@@ -3636,7 +3736,12 @@ static hipError_t launch_rollout_free_w(const RolloutArgs &a, size_t lds, hipStr
 hipError_t launch_rollout_free(const RolloutArgs &a, size_t lds, int waves, hipStream_t s) {
   if (a.s.nsub > 0 || a.s.act || a.s.mlp || !rollout_free_fits(a.s.nq, a.s.nb) || a.cap != a.s.ncon_max)
     return hipErrorInvalidValue;
-  return waves == 3 ? launch_rollout_free_w<3>(a, lds, s) : launch_rollout_free_w<4>(a, lds, s);
+  switch (waves) {
+    case 1: return launch_rollout_held_w<1>(a, lds, s);
+    case 2: return launch_rollout_held_w<2>(a, lds, s);
+    case 3: return launch_rollout_free_w<3>(a, lds, s);
+    default: return launch_rollout_free_w<4>(a, lds, s);
+  }
 }
 
 template <int CONDIM, bool ART>
