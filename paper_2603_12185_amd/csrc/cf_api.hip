@@ -633,11 +633,20 @@ static bool learned_k32(const cf_model *m) {
          cf::resolve_learned_k32_lds_bytes(m->nb, m->ng) <= kLdsLimit;
 }
 
+// The narrow phase of a step also writes the network's image where the
+// resolution that follows reads it.
+static void pack_net(const cf_model *m, cf::CollideArgs &ca) {
+  if (!m->mlp || !learned_k32(m)) return;
+  ca.pack_blocks = cf::mlp_pack_k32_blocks(m->block_collide);
+  ca.net = m->mlp;
+  ca.net_img = m->d_mlp_img;
+}
+
 // The resolution launch of a step: worlds of free bodies that fit the
 // workgroup one body per lane take the register-resident kernel; with learned
 // gains the network's LDS image is first written from the current parameters
-// (one small kernel), then the resolution copies it to LDS and runs at most
-// 128 threads per world.
+// (by the narrow phase's launch, pack_net, or one small kernel), then the
+// resolution copies it to LDS and runs at most 128 threads per world.
 static hipError_t launch_resolve_model(const cf_model *m, cf::ResolveArgs ra, hipStream_t s) {
   if (!m->mlp && !m->d_act && m->nsub == 0 && m->nb <= m->block_resolve)
     return cf::launch_resolve_free(ra, m->nw, m->block_resolve, m->lds_resolve_free, s);
@@ -645,8 +654,6 @@ static hipError_t launch_resolve_model(const cf_model *m, cf::ResolveArgs ra, hi
   if (learned_k32(m)) {
     ra.mlp = m->mlp;
     ra.mlp_img = m->d_mlp_img;
-    const hipError_t e = cf::launch_mlp_pack_k32(m->mlp, m->d_mlp_img, s);
-    if (e != hipSuccess) return e;
     return cf::launch_resolve_learned(ra, m->nw, cf::resolve_learned_k32_lds_bytes(m->nb, m->ng), s);
   }
   const int block = m->block_resolve > 128 ? 128 : m->block_resolve;
@@ -713,6 +720,7 @@ cf_status cf_step(cf_model *m, void *stream, const float *q, const float *v, con
     if (e != hipSuccess) return set_err(CF_E_DEVICE, std::string("step launch: ") + hipGetErrorString(e));
     return CF_OK;
   }
+  pack_net(m, ca);
   hipError_t e = cf::launch_collide(ca, m->nw, m->block_collide, m->lds_collide, s);
   if (e != hipSuccess) return set_err(CF_E_DEVICE, std::string("collide launch: ") + hipGetErrorString(e));
   if (ev && hipEventRecord(ev->e[1], s) != hipSuccess) return set_err(CF_E_DEVICE, "hipEventRecord failed");
@@ -1123,6 +1131,7 @@ cf_status cf_model_time_kernels(cf_model *m, void *stream, const float *q, const
   hipEvent_t e[3];
   for (auto &x : e)
     if (hipEventCreate(&x) != hipSuccess) return set_err(CF_E_DEVICE, "hipEventCreate failed");
+  pack_net(m, ca);
   hipError_t err = cf::launch_collide(ca, m->nw, m->block_collide, m->lds_collide, s);
   if (err == hipSuccess) err = hipEventRecord(e[0], s);
   for (int i = 0; i < reps && err == hipSuccess; ++i)

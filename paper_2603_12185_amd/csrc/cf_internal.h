@@ -116,6 +116,11 @@ struct CollideArgs {
                                 // rotation rows) for the resolution, or null
   int gpos_ws, gquat_ws;        // world stride in elements (0 = shared by all worlds)
   float margin;
+  // learned gains on the K = 32 resolution: the first pack_blocks workgroups of
+  // the narrow phase write the network's image for it (0: none do)
+  int pack_blocks;
+  const float *net;
+  void *net_img;
 };
 
 // Resolution kernel: one workgroup per world.
@@ -235,6 +240,6 @@ size_t rollout_held_lds_bytes(int nq, int nb, int ng, int norient, int nsph, int
 hipError_t launch_rollout_free(const RolloutArgs &a, size_t lds, int waves, hipStream_t s);
 hipError_t launch_resolve_learned(const ResolveArgs &a, int nworld, size_t lds, hipStream_t s);
 size_t mlp_image_k32_bytes();
-hipError_t launch_mlp_pack_k32(const float *params, void *img, hipStream_t s);
+int mlp_pack_k32_blocks(int block);  // CollideArgs::pack_blocks
 
 }  // namespace cf

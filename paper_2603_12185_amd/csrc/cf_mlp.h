@@ -165,49 +165,55 @@ struct WeightsK32 {
   float mean[NIN], istd[NIN];
 };
 
-// Pack the float32 parameters into WeightsK32 (all threads of the block; ends
-// with a barrier).
-template <int BS>
-__device__ inline void pack_weights_k32(const float *p, WeightsK32 *W) {
+// Pack record i of kPackRecords of the image from the float32 parameters.
+constexpr int kPackRecords = 4 * 16 + 4 * 2 * 64 + 2 * 64 + 16 + 4 + NIN;
+
+__device__ inline void pack_weights_k32(const float *p, WeightsK32 *W, int i) {
   auto in_of = [](int b, int k) {  // input unit of K index k of input block b
     const int g = k >> 3, t = k & 7;
     return 32 * b + (t < 4 ? 4 * g + t : 16 + 4 * g + t - 4);
   };
-  for (int i = threadIdx.x; i < 4 * 16; i += BS) {
-    const int m = i >> 4, row = i & 15;
-    bf16x8 v;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) v[t] = (__bf16)(t < NFEAT ? p[OFF_W1 + t * NH + 16 * m + row] : 0.f);
-    W->w1[m][row] = v;
-  }
-  for (int i = threadIdx.x; i < 4 * 2 * 64; i += BS) {
+  bf16x8 v;
+  if (i < 4 * 2 * 64) {
     const int m = i >> 7, b = (i >> 6) & 1, lane = i & 63;
     const int out = 16 * m + (lane & 15), g = lane >> 4;
-    bf16x8 v;
 #pragma unroll
     for (int t = 0; t < 8; ++t) v[t] = (__bf16)p[OFF_W2 + in_of(b, 8 * g + t) * NH + out];
     W->w2[m][b][lane] = v;
+    return;
   }
-  for (int i = threadIdx.x; i < 2 * 64; i += BS) {
+  i -= 4 * 2 * 64;
+  if (i < 2 * 64) {
     const int b = i >> 6, lane = i & 63;
     const int out = lane & 15, g = lane >> 4;
-    bf16x8 v;
 #pragma unroll
     for (int t = 0; t < 8; ++t) v[t] = (__bf16)p[OFF_W3 + in_of(b, 8 * g + t) * NOUT + out];
     W->w3[b][lane] = v;
+    return;
   }
-  for (int i = threadIdx.x; i < 16; i += BS) {
+  i -= 2 * 64;
+  if (i < 4 * 16) {
+    const int m = i >> 4, row = i & 15;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) v[t] = (__bf16)(t < NFEAT ? p[OFF_W1 + t * NH + 16 * m + row] : 0.f);
+    W->w1[m][row] = v;
+    return;
+  }
+  i -= 4 * 16;
+  if (i < 16) {
     const int m = i >> 2, g = i & 3, u = 16 * m + 4 * g;
     W->b1[i] = make_float4(p[OFF_B1 + u], p[OFF_B1 + u + 1], p[OFF_B1 + u + 2], p[OFF_B1 + u + 3]);
     W->b2[i] = make_float4(p[OFF_B2 + u], p[OFF_B2 + u + 1], p[OFF_B2 + u + 2], p[OFF_B2 + u + 3]);
+    return;
   }
-  for (int i = threadIdx.x; i < 4; i += BS)
+  i -= 16;
+  if (i < 4) {
     W->b3[i] = make_float4(p[OFF_B3 + 4 * i], p[OFF_B3 + 4 * i + 1], p[OFF_B3 + 4 * i + 2], p[OFF_B3 + 4 * i + 3]);
-  for (int i = threadIdx.x; i < NIN; i += BS) {
-    W->mean[i] = p[OFF_MEAN + i];
-    W->istd[i] = 1.0f / p[OFF_STD + i];
+    return;
   }
-  __syncthreads();
+  i -= 4;
+  W->mean[i] = p[OFF_MEAN + i];
+  W->istd[i] = 1.0f / p[OFF_STD + i];
 }
 
 __device__ inline f32x4 mfma32(bf16x8 a, bf16x8 b, f32x4 c) {
