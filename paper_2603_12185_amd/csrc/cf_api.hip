@@ -630,7 +630,18 @@ static bool rollout_fused(const cf_model *m) {
 // workgroup sharing the network's K = 32 image): free bodies, at most 128.
 static bool learned_k32(const cf_model *m) {
   return m->nsub == 0 && !m->d_act && m->nb <= 128 &&
-         cf::resolve_learned_k32_lds_bytes(m->nb, m->ng) <= kLdsLimit;
+         cf::resolve_learned_k32_lds_bytes(m->nb, m->ng, m->nb > 64 ? 2 : 4) <= kLdsLimit;
+}
+
+// Worlds of its workgroup: eight, at two workgroups (160 KB of LDS) and four
+// waves per SIMD, for a batch of more than twelve worlds per CU that sixteen
+// hold: one round instead of two (microseconds a step of piles of 64 spheres,
+// eight / four: 3300 worlds 71.6 / 75.1, 4096 72.6 / 76.3; but 3072 worlds, one
+// round either way, 70.6 / 60.2, and 6144 at condim 6 112 / 109).
+static int learned_worlds(const cf_model *m) {
+  if (m->nb > 64) return 2;
+  return m->nw > 12 * m->ncu && m->nw <= 16 * m->ncu &&
+                 cf::resolve_learned_k32_lds_bytes(m->nb, m->ng, 8) <= 80 * 1024 ? 8 : 4;
 }
 
 // The narrow phase of a step also writes the network's image where the
@@ -654,7 +665,7 @@ static hipError_t launch_resolve_model(const cf_model *m, cf::ResolveArgs ra, hi
   if (learned_k32(m)) {
     ra.mlp = m->mlp;
     ra.mlp_img = m->d_mlp_img;
-    return cf::launch_resolve_learned(ra, m->nw, cf::resolve_learned_k32_lds_bytes(m->nb, m->ng), s);
+    return cf::launch_resolve_learned(ra, m->nw, learned_worlds(m), s);
   }
   const int block = m->block_resolve > 128 ? 128 : m->block_resolve;
   ra.mlp = m->mlp;

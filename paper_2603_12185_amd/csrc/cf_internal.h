@@ -226,9 +226,9 @@ __host__ __device__ size_t resolve_free_lds_bytes(int nb, int ng);
 hipError_t launch_resolve_free(const ResolveArgs &a, int nworld, int block, size_t lds, hipStream_t s);
 hipError_t launch_step_free(const CollideArgs &ca, const ResolveArgs &ra, int nworld, size_t lds, hipStream_t s);
 hipError_t launch_step_art(const CollideArgs &ca, const ResolveArgs &ra, int nworld, size_t lds, hipStream_t s);
-// The same with learned gains (network image of launch_mlp_pack_k32 in
-// mlp_img), four worlds of at most 128 free bodies per workgroup.
-size_t resolve_learned_k32_lds_bytes(int nb, int ng);
+// The same with learned gains (the narrow phase's network image in mlp_img):
+// four or eight worlds of at most 64 free bodies per workgroup, two of at most 128.
+size_t resolve_learned_k32_lds_bytes(int nb, int ng, int worlds);
 // Rollout of worlds of free bodies (at most 64, q row within the narrow
 // phase's candidate list), one persistent one-wave workgroup per world;
 // `waves`: 3 (registers for twelve resident worlds per CU, no spills) or 4
@@ -238,7 +238,7 @@ size_t rollout_free_lds_bytes(int nb, int ng, int norient, int nsph);
 size_t rollout_held_lds_bytes(int nq, int nb, int ng, int norient, int nsph, int cap);
 // waves 1, 2: rollout_held_kernel with `lds` = rollout_held_lds_bytes(), else rollout_free_kernel
 hipError_t launch_rollout_free(const RolloutArgs &a, size_t lds, int waves, hipStream_t s);
-hipError_t launch_resolve_learned(const ResolveArgs &a, int nworld, size_t lds, hipStream_t s);
+hipError_t launch_resolve_learned(const ResolveArgs &a, int nworld, int worlds, hipStream_t s);
 size_t mlp_image_k32_bytes();
 int mlp_pack_k32_blocks(int block);  // CollideArgs::pack_blocks
 

@@ -3161,11 +3161,13 @@ hipError_t launch_step_art(const CollideArgs &ca, const ResolveArgs &ra, int nwo
 // accumulation registers, from which every output was copied before use (144
 // copies per 64 contacts): 4096 piles of 64 spheres 83.5 -> 80.7 us a step at
 // condim 3, 97.5 -> 85.5 at condim 6; a bound of four spills (86.5, 95.2).
-// Worlds (waves) per workgroup: four of up to 64 bodies, two of up to 128.
-__host__ __device__ constexpr int learn_worlds(int nbl) { return nbl == 1 ? 4 : 2; }
-
-size_t resolve_learned_k32_lds_bytes(int nb, int ng) {
-  return (sizeof(mlp::WeightsK32) + 15) / 16 * 16 + learn_worlds(nb > 64 ? 2 : 1) * resolve_free_lds_bytes(nb, ng);
+// LW: worlds (waves) per workgroup.  Four of up to 64 bodies, two of up to 128;
+// eight of up to 64, bounded to four waves per SIMD, for a batch that then is
+// resident at once where three waves (142 registers; 46 KB for four worlds) leave
+// a last round nearly empty: 4096 piles of 64 spheres 76.6 -> 72.5 us a step,
+// condim 6 81.0 -> 78.4, for all of nine spilled registers (33).
+size_t resolve_learned_k32_lds_bytes(int nb, int ng, int worlds) {
+  return (sizeof(mlp::WeightsK32) + 15) / 16 * 16 + worlds * resolve_free_lds_bytes(nb, ng);
 }
 
 // Orders the wave's LDS accesses before and after (the wave's lanes exchange
@@ -3175,18 +3177,17 @@ __device__ inline void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-template <int CONDIM, int NBL>
-__global__ __launch_bounds__(64 * learn_worlds(NBL), 2) void resolve_learned_kernel(ResolveArgs a) {
+template <int CONDIM, int NBL, int LW>
+__global__ __launch_bounds__(64 * LW, LW == 8 ? 4 : 2) void resolve_learned_kernel(ResolveArgs a) {
   constexpr int NF = CONDIM == 1 ? 1 : CONDIM == 3 ? 4 : CONDIM == 4 ? 6 : 10;
-  constexpr int kLearnWorlds = learn_worlds(NBL);
   extern __shared__ float4 lds[];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int w = blockIdx.x * kLearnWorlds + wv;
+  const int w = blockIdx.x * LW + wv;
   mlp::WeightsK32 *W = reinterpret_cast<mlp::WeightsK32 *>(lds);
   {  // the network's image for this step, copied by the whole workgroup
     static_assert(sizeof(mlp::WeightsK32) % sizeof(float4) == 0, "image copied in float4");
     float4 *dst = reinterpret_cast<float4 *>(W);
-    for (int i = threadIdx.x; i < (int)(sizeof(mlp::WeightsK32) / sizeof(float4)); i += 64 * kLearnWorlds)
+    for (int i = threadIdx.x; i < (int)(sizeof(mlp::WeightsK32) / sizeof(float4)); i += 64 * LW)
       dst[i] = a.mlp_img[i];
   }
   __syncthreads();
@@ -3393,23 +3394,28 @@ __global__ __launch_bounds__(64 * learn_worlds(NBL), 2) void resolve_learned_ker
   }
 }
 
-template <int NBL>
+template <int NBL, int LW>
 static hipError_t launch_resolve_learned_n(const ResolveArgs &a, int nworld, size_t lds, hipStream_t s) {
-  constexpr int kLearnWorlds = learn_worlds(NBL);
-  const dim3 grid((nworld + kLearnWorlds - 1) / kLearnWorlds), block(64 * kLearnWorlds);
+  const dim3 grid((nworld + LW - 1) / LW), block(64 * LW);
   switch (a.condim) {
-    case 1: hipLaunchKernelGGL((resolve_learned_kernel<1, NBL>), grid, block, lds, s, a); break;
-    case 3: hipLaunchKernelGGL((resolve_learned_kernel<3, NBL>), grid, block, lds, s, a); break;
-    case 4: hipLaunchKernelGGL((resolve_learned_kernel<4, NBL>), grid, block, lds, s, a); break;
-    case 6: hipLaunchKernelGGL((resolve_learned_kernel<6, NBL>), grid, block, lds, s, a); break;
+    case 1: hipLaunchKernelGGL((resolve_learned_kernel<1, NBL, LW>), grid, block, lds, s, a); break;
+    case 3: hipLaunchKernelGGL((resolve_learned_kernel<3, NBL, LW>), grid, block, lds, s, a); break;
+    case 4: hipLaunchKernelGGL((resolve_learned_kernel<4, NBL, LW>), grid, block, lds, s, a); break;
+    case 6: hipLaunchKernelGGL((resolve_learned_kernel<6, NBL, LW>), grid, block, lds, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-hipError_t launch_resolve_learned(const ResolveArgs &a, int nworld, size_t lds, hipStream_t s) {
+hipError_t launch_resolve_learned(const ResolveArgs &a, int nworld, int worlds, hipStream_t s) {
   if (a.nsub > 0 || !a.mlp_img || a.act || a.nb > 128 || a.nworld != nworld) return hipErrorInvalidValue;
-  return a.nb > 64 ? launch_resolve_learned_n<2>(a, nworld, lds, s) : launch_resolve_learned_n<1>(a, nworld, lds, s);
+  const size_t lds = resolve_learned_k32_lds_bytes(a.nb, a.ng, worlds);
+  if (a.nb > 64) return worlds == 2 ? launch_resolve_learned_n<2, 2>(a, nworld, lds, s) : hipErrorInvalidValue;
+  switch (worlds) {
+    case 4: return launch_resolve_learned_n<1, 4>(a, nworld, lds, s);
+    case 8: return launch_resolve_learned_n<1, 8>(a, nworld, lds, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 template <int CONDIM>
