@@ -646,11 +646,9 @@ static int learned_worlds(const cf_model *m) {
 
 // The narrow phase of a step also writes the network's image where the
 // resolution that follows reads it.
-static void pack_net(const cf_model *m, cf::CollideArgs &ca) {
-  if (!m->mlp || !learned_k32(m)) return;
-  ca.pack_blocks = cf::mlp_pack_k32_blocks(m->block_collide);
-  ca.net = m->mlp;
-  ca.net_img = m->d_mlp_img;
+static cf::PackArgs pack_net(const cf_model *m) {
+  if (!m->mlp || !learned_k32(m)) return {};
+  return {cf::mlp_pack_k32_blocks(m->block_collide), m->mlp, m->d_mlp_img};
 }
 
 // The resolution launch of a step: worlds of free bodies that fit the
@@ -731,8 +729,7 @@ cf_status cf_step(cf_model *m, void *stream, const float *q, const float *v, con
     if (e != hipSuccess) return set_err(CF_E_DEVICE, std::string("step launch: ") + hipGetErrorString(e));
     return CF_OK;
   }
-  pack_net(m, ca);
-  hipError_t e = cf::launch_collide(ca, m->nw, m->block_collide, m->lds_collide, s);
+  hipError_t e = cf::launch_collide(ca, pack_net(m), m->nw, m->block_collide, m->lds_collide, s);
   if (e != hipSuccess) return set_err(CF_E_DEVICE, std::string("collide launch: ") + hipGetErrorString(e));
   if (ev && hipEventRecord(ev->e[1], s) != hipSuccess) return set_err(CF_E_DEVICE, "hipEventRecord failed");
 
@@ -820,7 +817,7 @@ cf_status cf_step_backward(cf_model *m, void *stream, const float *q, const floa
   }
   cf::CollideArgs ca = collide_args(m);
   ca.q = q;
-  hipError_t e = cf::launch_collide(ca, m->nw, m->block_collide, m->lds_collide, s);
+  hipError_t e = cf::launch_collide(ca, {}, m->nw, m->block_collide, m->lds_collide, s);
   if (e != hipSuccess) return set_err(CF_E_DEVICE, std::string("collide launch: ") + hipGetErrorString(e));
   cf::BackwardArgs b = backward_args(m);
   b.s.q = q; b.s.v = v; b.s.tau = tau;
@@ -916,7 +913,7 @@ cf_status cf_rollout(cf_model *m, void *stream, int32_t T, const float *q0, cons
     // eight worlds (two waves per SIMD) still share a CU's 160 KB with them
     size_t lds = (m->lds_rollout + 15) / 16 * 16;
     const size_t consts = cf::rollout_const_bytes(m->nb, m->ng, m->nv, m->nsub);
-    if (m->nsub > 0 && m->block_rollout == 64 && lds + consts <= 20 * 1024) {
+    if (m->nsub > 0 && m->block_rollout == 64 && lds + consts <= 20 * 1024 && m->nsph <= cf::kDirectSpheres) {
       r.const_ofs = (int)(lds / 16);
       lds += consts;
     }
@@ -1142,11 +1139,10 @@ cf_status cf_model_time_kernels(cf_model *m, void *stream, const float *q, const
   hipEvent_t e[3];
   for (auto &x : e)
     if (hipEventCreate(&x) != hipSuccess) return set_err(CF_E_DEVICE, "hipEventCreate failed");
-  pack_net(m, ca);
-  hipError_t err = cf::launch_collide(ca, m->nw, m->block_collide, m->lds_collide, s);
+  hipError_t err = cf::launch_collide(ca, pack_net(m), m->nw, m->block_collide, m->lds_collide, s);
   if (err == hipSuccess) err = hipEventRecord(e[0], s);
   for (int i = 0; i < reps && err == hipSuccess; ++i)
-    err = cf::launch_collide(ca, m->nw, m->block_collide, m->lds_collide, s);
+    err = cf::launch_collide(ca, pack_net(m), m->nw, m->block_collide, m->lds_collide, s);
   if (err == hipSuccess) err = hipEventRecord(e[1], s);
   for (int i = 0; i < reps && err == hipSuccess; ++i)
     err = launch_resolve_model(m, ra, s);

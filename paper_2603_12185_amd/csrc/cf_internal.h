@@ -89,6 +89,8 @@ struct PlanePose {
   double nd[4], pd[4]; // float64 normal and position
 };
 
+constexpr int kDirectSpheres = 40;  // sphere blocks up to this size are tested slot by slot
+
 // Collision kernel: one workgroup per world.
 struct CollideArgs {
   const float *q;               // [nw][nq]
@@ -116,11 +118,14 @@ struct CollideArgs {
                                 // rotation rows) for the resolution, or null
   int gpos_ws, gquat_ws;        // world stride in elements (0 = shared by all worlds)
   float margin;
-  // learned gains on the K = 32 resolution: the first pack_blocks workgroups of
-  // the narrow phase write the network's image for it (0: none do)
-  int pack_blocks;
+};
+
+// Learned gains on the K = 32 resolution: the first `blocks` workgroups of the
+// narrow phase write the network's image for it (0: none do).
+struct PackArgs {
+  int blocks;
   const float *net;
-  void *net_img;
+  void *img;
 };
 
 // Resolution kernel: one workgroup per world.
@@ -218,7 +223,7 @@ size_t rollout_const_bytes(int nb, int ng, int nv, int nsub);
 hipError_t launch_rollout(const RolloutArgs &a, int block, size_t lds, hipStream_t s);
 size_t resolve_lds_bytes(int nq, int nv, int nb, int ng, int nsub, int art_floats);
 size_t resolve_learned_lds_bytes(int block);  // extra LDS of the resolution with learned gains
-hipError_t launch_collide(const CollideArgs &a, int nworld, int block, size_t lds, hipStream_t s);
+hipError_t launch_collide(const CollideArgs &a, const PackArgs &p, int nworld, int block, size_t lds, hipStream_t s);
 hipError_t launch_resolve(const ResolveArgs &a, int nworld, int block, size_t lds, hipStream_t s);
 // Resolution of worlds of free bodies (no subtrees, actuators or learned
 // gains) with at most `block` bodies, each body's state in its lane.
@@ -240,6 +245,6 @@ size_t rollout_held_lds_bytes(int nq, int nb, int ng, int norient, int nsph, int
 hipError_t launch_rollout_free(const RolloutArgs &a, size_t lds, int waves, hipStream_t s);
 hipError_t launch_resolve_learned(const ResolveArgs &a, int nworld, int worlds, hipStream_t s);
 size_t mlp_image_k32_bytes();
-int mlp_pack_k32_blocks(int block);  // CollideArgs::pack_blocks
+int mlp_pack_k32_blocks(int block);  // PackArgs::blocks
 
 }  // namespace cf

@@ -1154,7 +1154,6 @@ __device__ inline void sphere_pair_record(float4 A, float4 B, uint32_t sl, float
 // Sphere blocks of up to this many spheres test their pairs slot by slot: a step
 // of 4096 piles of 16 / 32 / 40 / 45 spheres takes 12.2 / 16.6 / 18.7 / 21.7 us so,
 // 13.5 / 18.1 / 20.2 / 21.4 us through masks.
-constexpr int kDirectSpheres = 40;
 static_assert(kDirectSpheres * (kDirectSpheres - 1) / 2 <= kCandCap, "every pair fits the candidate list");
 
 template <int BS, int NWD>
@@ -1398,7 +1397,7 @@ __device__ int collide_world(const CollideArgs &a, int w, const float *sq, float
     const float4 gp = gi.gp, gd = gi.gd, gq = gi.gq;
     go[g] = o;
     gbd[g] = b;
-    if (g < a.npl) {  // a plane of the plane rows: its pose is a model constant, its sizes enter the band
+    if (!ART && g < a.npl) {  // a plane of the plane rows: its pose is a model constant, its sizes enter the band
       Gs[g] = make_float4(gp.x, gp.y, gp.z, fmaxf(fmaxf(gd.x, gd.y), gd.z));
       return;
     }
@@ -1471,7 +1470,7 @@ __device__ int collide_world(const CollideArgs &a, int w, const float *sq, float
       const float4 G = Gs[g];
       ext = fmaxf(ext, fmaxf(fmaxf(fabsf(G.x), fabsf(G.y)), fmaxf(fabsf(G.z), G.w)));
     }
-    for (int o = a.npl > 0 ? a.norient : tid; o < a.norient; o += BS)  // (with plane rows no other geom is oriented)
+    for (int o = !ART && a.npl > 0 ? a.norient : tid; o < a.norient; o += BS)  // (with plane rows no other geom is oriented)
       ext = fmaxf(ext, fmaxf(fmaxf(Of[o].s[0], Of[o].s[1]), Of[o].s[2]));
     ext = block_max<BS>(ext, wmax);
     band = 1e-4f + 8e-6f * ext;
@@ -1728,15 +1727,15 @@ __device__ int collide_world(const CollideArgs &a, int w, const float *sq, float
 }
 
 template <int BS, bool ART>
-__global__ __launch_bounds__(BS) void collide_kernel(CollideArgs a) {
+__global__ __launch_bounds__(BS) void collide_kernel(CollideArgs a, PackArgs pk) {
   extern __shared__ float4 lds[];
-  const int w = (int)blockIdx.x - a.pack_blocks, tid = threadIdx.x;
+  const int w = (int)blockIdx.x - pk.blocks, tid = threadIdx.x;
   if (w < 0) {
     // Learned gains: one record of the network's image per thread, beside the
     // worlds' narrow phases (by one workgroup of a kernel of its own, 4.8 us of
     // a step: 4096 piles of 64 spheres 76.9 -> 74.1 us; 512 of 40 24.8 -> 22.4).
     const int i = blockIdx.x * BS + tid;
-    if (i < mlp::kPackRecords) mlp::pack_weights_k32(a.net, reinterpret_cast<mlp::WeightsK32 *>(a.net_img), i);
+    if (i < mlp::kPackRecords) mlp::pack_weights_k32(pk.net, reinterpret_cast<mlp::WeightsK32 *>(pk.img), i);
     return;
   }
   float *sq = reinterpret_cast<float *>(lds);
@@ -1796,19 +1795,19 @@ size_t collide_lds_bytes(int nq, int nb, int ng, int norient, int nsub, int nsph
 int mlp_pack_k32_blocks(int block) { return (mlp::kPackRecords + block - 1) / block; }
 
 template <bool ART>
-static hipError_t launch_collide_a(const CollideArgs &a, int nworld, int block, size_t lds, hipStream_t s) {
+static hipError_t launch_collide_a(const CollideArgs &a, const PackArgs &p, int nworld, int block, size_t lds, hipStream_t s) {
   switch (block) {
-    case 64: hipLaunchKernelGGL((collide_kernel<64, ART>), dim3(a.pack_blocks + nworld), dim3(64), lds, s, a); break;
-    case 128: hipLaunchKernelGGL((collide_kernel<128, ART>), dim3(a.pack_blocks + nworld), dim3(128), lds, s, a); break;
-    case 256: hipLaunchKernelGGL((collide_kernel<256, ART>), dim3(a.pack_blocks + nworld), dim3(256), lds, s, a); break;
+    case 64: hipLaunchKernelGGL((collide_kernel<64, ART>), dim3(p.blocks + nworld), dim3(64), lds, s, a, p); break;
+    case 128: hipLaunchKernelGGL((collide_kernel<128, ART>), dim3(p.blocks + nworld), dim3(128), lds, s, a, p); break;
+    case 256: hipLaunchKernelGGL((collide_kernel<256, ART>), dim3(p.blocks + nworld), dim3(256), lds, s, a, p); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-hipError_t launch_collide(const CollideArgs &a, int nworld, int block, size_t lds, hipStream_t s) {
-  return a.nsub > 0 ? launch_collide_a<true>(a, nworld, block, lds, s)
-                    : launch_collide_a<false>(a, nworld, block, lds, s);
+hipError_t launch_collide(const CollideArgs &a, const PackArgs &p, int nworld, int block, size_t lds, hipStream_t s) {
+  return a.nsub > 0 ? launch_collide_a<true>(a, p, nworld, block, lds, s)
+                    : launch_collide_a<false>(a, p, nworld, block, lds, s);
 }
 
 // ====================================================================
@@ -3463,7 +3462,9 @@ static_assert(sizeof(BodyC) % sizeof(float4) == 0 && sizeof(SubTree) == 10 * siz
 // constants from L2 and passed the subtrees' frames through it.
 // They are copied to LDS once and the narrow phase and the resolution read
 // them, and the frames, there (the same arithmetic, bit for bit): a batch of
-// 2048 hands and 20 steps takes 430 us in the kernel, 505 us before.
+// 2048 hands and 20 steps takes 430 us in the kernel, 505 us before.  Such worlds
+// hold at most kDirectSpheres in the sphere block, so it leaves out the mask code
+// (the same batch with its scores: 484 us, 494 with that code's spills).
 template <int CONDIM, int BS, bool ART, bool LC>
 __global__ __launch_bounds__(BS, 2) void rollout_kernel(RolloutArgs r) {
   extern __shared__ float4 lds[];
@@ -3532,7 +3533,7 @@ __global__ __launch_bounds__(BS, 2) void rollout_kernel(RolloutArgs r) {
     float4 mi0 = make_float4(1.f, 1.f, 1.f, 1.f);
     if (tid < nb) mi0 = ra.bmi[(size_t)wc * nb + tid];
     __syncthreads();
-    const int found = collide_world<BS, ART>(ca, wc, sq, reg, cn, cp, cap, nxt);
+    const int found = collide_world<BS, ART, LC ? 1 : 0>(ca, wc, sq, reg, cn, cp, cap, nxt);
     const int nc = found < cap ? found : cap;
     float4 c0n = make_float4(0.f, 0.f, 0.f, 0.f), c0p = c0n;
     if (tid < nc) {
@@ -3763,6 +3764,7 @@ hipError_t launch_rollout_free(const RolloutArgs &a, size_t lds, int waves, hipS
 template <int CONDIM, bool ART>
 static hipError_t launch_rollout_b(const RolloutArgs &a, int block, size_t lds, hipStream_t s) {
   if (ART && block == 64 && a.const_ofs > 0) {
+    if (a.c.nsph > kDirectSpheres) return hipErrorInvalidValue;
     hipLaunchKernelGGL((rollout_kernel<CONDIM, 64, ART, ART>), dim3(a.nworld), dim3(64), lds, s, a);
     return hipGetLastError();
   }
