@@ -513,6 +513,8 @@ cf_status cf_model_create(const cf_model_desc *d, cf_model **out) {
 
   hipError_t e = hipSuccess;
   auto chk = [&](hipError_t r) { if (e == hipSuccess) e = r; };
+  slots.insert(slots.begin(), cf::kSlotPad, 0u);  // words around the table that prefetches may read
+  slots.push_back(0u);
   chk(upload(&m->d_slots, slots));
   chk(upload(&m->d_gbody, gbody));
   chk(upload(&m->d_gorient, gorient));
@@ -577,7 +579,7 @@ static cf::CollideArgs collide_args(const cf_model *m) {
   ca.gorient = m->d_gorient; ca.norient = m->norient;
   ca.body = m->d_body; ca.sub = m->d_sub; ca.nsub = m->nsub; ca.jk = m->d_jk64;
   ca.frames = m->d_frames;
-  ca.slots = m->d_slots; ca.cnp = m->d_cnp; ca.cpos = m->d_cpos; ca.ncon = m->d_ncon; ca.overflow = m->d_over;
+  ca.slots = m->d_slots + cf::kSlotPad; ca.cnp = m->d_cnp; ca.cpos = m->d_cpos; ca.ncon = m->d_ncon; ca.overflow = m->d_over;
   ca.nq = m->nq; ca.nb = m->nb; ca.ng = m->ng; ca.nslot = m->nslot; ca.ncon_max = m->ncon_max;
   ca.gpos_ws = m->gpos_ws; ca.gquat_ws = m->gquat_ws; ca.margin = m->p.margin;
   ca.nslot_pre = m->nslot_pre; ca.sph0 = m->sph0; ca.nsph = m->nsph; ca.npl = m->npl; ca.sph_mfma = m->sph_mfma;

@@ -91,6 +91,12 @@ struct PlanePose {
 
 constexpr int kDirectSpheres = 40;  // sphere blocks up to this size are tested slot by slot
 
+// Words before the slot table (whole cache lines, so that its rows stay aligned;
+// one more follows it).  A prefetch clamped to a range's last slot reads the word
+// before an empty range: the one before the table where a block of spheres
+// without pairs is all there is.
+constexpr int kSlotPad = 64;
+
 // Collision kernel: one workgroup per world.
 struct CollideArgs {
   const float *q;               // [nw][nq]
@@ -101,7 +107,7 @@ struct CollideArgs {
   const int *gorient;           // [ng] index among oriented geoms, -1 for a plain sphere
   const BodyC *body;            // [nb]
   const SubTree *sub;           // [nsub]
-  const uint32_t *slots;        // [nslot] canonical order
+  const uint32_t *slots;        // [-kSlotPad .. nslot], slots 0 .. nslot - 1 in canonical order
   float4 *cnp;                  // [nw][ncon_max] (n.x, n.y, n.z, phi)
   float4 *cpos;                 // [nw][ncon_max] (p.x, p.y, p.z, slot bits)
   int *ncon, *overflow;         // [nw] model workspace

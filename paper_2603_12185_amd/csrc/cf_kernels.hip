@@ -1604,6 +1604,8 @@ __device__ int collide_world(const CollideArgs &a, int w, const float *sq, float
     // few pairs: one slot of the block per lane and pass, hits compacted in slot
     // order (their records at once when one pass covers the pairs, else from
     // the candidate list), without masks, their transposition and a row scan
+    // (np = 0 where the block's spheres share a body or are all static: the
+    // prefetches then read the word before the block's slots, kSlotPad)
     const int np = a.nslot - a.nslot_pre;
     const uint32_t *slots = a.slots + a.nslot_pre;
     uint32_t sl1 = slots[min(tid, np - 1)], sl2 = slots[min(tid + BS, np - 1)];
