@@ -787,6 +787,31 @@ static cf::AdjointArgs adjoint_args(const cf_model *m) {
   return r;
 }
 
+// The adjoint of one step; the incoming adjoints, read by single floats, may
+// begin anywhere (a trajectory's row) and be gq, gv themselves.
+static cf_status step_adjoint(cf_model *m, hipStream_t s, const float *q, const float *v, const float *tau,
+                              const float *gq_out, const float *gv_out, float *gq, float *gv, float *gtau) {
+  if (adjoint_free(m, 1)) {
+    cf::AdjointArgs r = adjoint_args(m);
+    r.q_traj = q; r.v_traj = v; r.tau_seq = tau; r.gq_end = gq_out; r.gv_end = gv_out;
+    r.gq = gq; r.gv = gv; r.gtau = gtau; r.T = 1;
+    const hipError_t e = cf::launch_adjoint_free(r, m->lds_adjoint_free, s);
+    if (e != hipSuccess) return set_err(CF_E_DEVICE, std::string("adjoint launch: ") + hipGetErrorString(e));
+    return CF_OK;
+  }
+  cf::CollideArgs ca = collide_args(m);
+  ca.q = q;
+  hipError_t e = cf::launch_collide(ca, {}, m->nw, m->block_collide, m->lds_collide, s);
+  if (e != hipSuccess) return set_err(CF_E_DEVICE, std::string("collide launch: ") + hipGetErrorString(e));
+  cf::BackwardArgs b = backward_args(m);
+  b.s.q = q; b.s.v = v; b.s.tau = tau;
+  b.gq_out = gq_out; b.gv_out = gv_out; b.gq = gq; b.gv = gv; b.gtau = gtau;
+  const int l = m->mlp ? 1 : 0;
+  e = cf::launch_backward(b, m->nw, m->block_backward[l], m->lds_backward[l], s);
+  if (e != hipSuccess) return set_err(CF_E_DEVICE, std::string("backward launch: ") + hipGetErrorString(e));
+  return CF_OK;
+}
+
 cf_status cf_step_backward(cf_model *m, void *stream, const float *q, const float *v, const float *tau,
                            const float *gq_out, const float *gv_out, float *gq, float *gv, float *gtau) {
   if (!m) return set_err(CF_E_INVALID_ARG, "model is NULL");
@@ -808,26 +833,7 @@ cf_status cf_step_backward(cf_model *m, void *stream, const float *q, const floa
       overlap(gtau, sv, gq_out, sq) || overlap(gtau, sv, gv_out, sv))
     return set_err(CF_E_INVALID_ARG, "gq/gv may alias gq_out/gv_out only exactly; no other overlap");
   if (const cf_status st = adjoint_supported(m); st != CF_OK) return st;
-  hipStream_t s = (hipStream_t)stream;
-  if (adjoint_free(m, 1)) {
-    cf::AdjointArgs r = adjoint_args(m);
-    r.q_traj = q; r.v_traj = v; r.tau_seq = tau; r.gq_end = gq_out; r.gv_end = gv_out;
-    r.gq = gq; r.gv = gv; r.gtau = gtau; r.T = 1;
-    const hipError_t e = cf::launch_adjoint_free(r, m->lds_adjoint_free, s);
-    if (e != hipSuccess) return set_err(CF_E_DEVICE, std::string("adjoint launch: ") + hipGetErrorString(e));
-    return CF_OK;
-  }
-  cf::CollideArgs ca = collide_args(m);
-  ca.q = q;
-  hipError_t e = cf::launch_collide(ca, {}, m->nw, m->block_collide, m->lds_collide, s);
-  if (e != hipSuccess) return set_err(CF_E_DEVICE, std::string("collide launch: ") + hipGetErrorString(e));
-  cf::BackwardArgs b = backward_args(m);
-  b.s.q = q; b.s.v = v; b.s.tau = tau;
-  b.gq_out = gq_out; b.gv_out = gv_out; b.gq = gq; b.gv = gv; b.gtau = gtau;
-  const int l = m->mlp ? 1 : 0;
-  e = cf::launch_backward(b, m->nw, m->block_backward[l], m->lds_backward[l], s);
-  if (e != hipSuccess) return set_err(CF_E_DEVICE, std::string("backward launch: ") + hipGetErrorString(e));
-  return CF_OK;
+  return step_adjoint(m, (hipStream_t)stream, q, v, tau, gq_out, gv_out, gq, gv, gtau);
 }
 
 cf_status cf_rollout_backward(cf_model *m, void *stream, int32_t T, const float *q_traj, const float *v_traj,
@@ -868,9 +874,9 @@ cf_status cf_rollout_backward(cf_model *m, void *stream, int32_t T, const float 
   }
   for (int t = T - 1; t >= 0; --t) {
     const bool last = t == T - 1;
-    const cf_status st = cf_step_backward(m, stream, q_traj + t * sq, v_traj + t * sv, tau_seq ? tau_seq + t * sv : nullptr,
-                                          last ? gqT : gq0, last ? gvT : gv0, gq0, gv0,
-                                          gtau_seq ? gtau_seq + t * sv : nullptr);
+    const cf_status st = step_adjoint(m, s, q_traj + t * sq, v_traj + t * sv, tau_seq ? tau_seq + t * sv : nullptr,
+                                      last ? gqT : gq0, last ? gvT : gv0, gq0, gv0,
+                                      gtau_seq ? gtau_seq + t * sv : nullptr);
     if (st != CF_OK) return st;
     hipError_t e = hipSuccess;
     if (gq_traj) e = cf::launch_add_rows(gq0, gq_traj + t * sq, sq, s);
