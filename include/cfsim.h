@@ -202,7 +202,8 @@ cf_status cf_step_backward(cf_model *m, void *stream, const float *q, const floa
  * of every state (either may be NULL = zero).  Writes gq0 [nworld][nq] and gv0
  * [nworld][nv], the adjoints of the initial state, and gtau_seq [T][nworld][nv]
  * (may be NULL).  T >= 1; buffers and, for T > 1, every step's rows 16-byte
- * aligned; outputs overlap nothing.  Worlds of at most 64 free bodies without
+ * aligned, but gq_traj and gv_traj, which may begin at any float; outputs
+ * overlap nothing.  Worlds of at most 64 free bodies without
  * learned gains run all T steps in one kernel launch; other models take T
  * cf_step_backward calls on the stream.  Allocates nothing. */
 cf_status cf_rollout_backward(cf_model *m, void *stream, int32_t T, const float *q_traj, const float *v_traj,

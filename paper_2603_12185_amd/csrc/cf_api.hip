@@ -843,9 +843,11 @@ cf_status cf_rollout_backward(cf_model *m, void *stream, int32_t T, const float 
   if (T < 1) return set_err(CF_E_INVALID_ARG, "T must be >= 1");
   if (!q_traj || !v_traj || !gq0 || !gv0) return set_err(CF_E_INVALID_ARG, "q_traj, v_traj, gq0, gv0 must be non-NULL");
   const size_t sq = (size_t)m->nw * m->nq, sv = (size_t)m->nw * m->nv;
-  const float *ptrs[] = {q_traj, v_traj, tau_seq, gq_traj, gv_traj, gq0, gv0, gtau_seq};
+  const float *ptrs[] = {q_traj, v_traj, tau_seq, gq0, gv0, gtau_seq};
   for (const float *p : ptrs)
     if (p && !aligned16(p)) return set_err(CF_E_INVALID_ARG, "buffers must be 16-byte aligned");
+  if (((uintptr_t)gq_traj | (uintptr_t)gv_traj) & 3u)  // read by single floats
+    return set_err(CF_E_INVALID_ARG, "adjoints must be 4-byte aligned");
   if (T > 1 && (sq % 4 || sv % 4)) return set_err(CF_E_INVALID_ARG, "trajectory rows must be 16-byte aligned");
   auto overlap = [](const float *x, size_t nx, const float *y, size_t ny) {
     return x && y && x < y + ny && y < x + nx;

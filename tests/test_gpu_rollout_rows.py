@@ -40,3 +40,36 @@ def test_one_step_of_odd_rows(name):
     a, b, _ = m.step_backward(q0.detach(), v0.detach(), None, gq_t[1].clone(), gv_t[1].clone())
     for x, y in ((gq, a + gq_t[0]), (gv, b + gv_t[0])):  # the same sums, but for one fused rounding
         assert float((x.double() - y.double()).norm() / y.double().norm()) <= 1e-6
+
+
+# gradients that begin one to three floats into a buffer
+@pytest.mark.parametrize("T", [1, 3])
+@pytest.mark.parametrize("name", ["pushers 4", "hand 4", "spheres 41 4"])
+def test_gradient_off_16_bytes(name, T):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_12185_amd import autograd
+    print(f"case: gradient off 16 bytes, {name}, T {T}", flush=True)
+    s, m = _model(name)
+    q0, v0 = tdev(s["q0"]).requires_grad_(True), tdev(s["v0"]).requires_grad_(True)
+    q, v = autograd.rollout(m, T, q0, v0)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    buf = torch.randn(3 + max(q.numel(), v.numel()), generator=g, device="cuda")
+    ref = None
+    for clone in (True, False):
+        for k in (1, 2, 3):
+            gq, gv = buf[k:k + q.numel()].view(q.shape), buf[4 - k:4 - k + v.numel()].view(v.shape)
+            assert gq.data_ptr() % 16 and gv.data_ptr() % 16
+            if clone:
+                gq, gv = gq.clone(), gv.clone()
+            out = torch.autograd.grad([q, v], [q0, v0], [gq, gv], retain_graph=True)
+            if clone:
+                ref = (ref or []) + [out]
+            else:
+                assert torch.equal(out[0], ref[k - 1][0]) and torch.equal(out[1], ref[k - 1][1])
+    # the slice that a concatenation's gradient is
+    cost = torch.cat((q.sum().view(1), q.flatten()))
+    gq, = torch.autograd.grad(cost, [q0], torch.ones_like(cost))
+    assert torch.isfinite(gq).all()
