@@ -1728,11 +1728,15 @@ __device__ int collide_world(const CollideArgs &a, int w, const float *sq, float
   return running;
 }
 
-template <int BS, bool ART>
+// PACK: the first workgroups write the network's image.  Only steps that need it
+// take that kernel: the branch waits for the number of those workgroups before
+// any other argument is loaded, 0.4 us of every launch (a step of 256 hands
+// 20.5 us without, 20.9 with it).
+template <int BS, bool ART, bool PACK>
 __global__ __launch_bounds__(BS) void collide_kernel(CollideArgs a, PackArgs pk) {
   extern __shared__ float4 lds[];
-  const int w = (int)blockIdx.x - pk.blocks, tid = threadIdx.x;
-  if (w < 0) {
+  const int w = (int)blockIdx.x - (PACK ? pk.blocks : 0), tid = threadIdx.x;
+  if (PACK && w < 0) {
     // Learned gains: one record of the network's image per thread, beside the
     // worlds' narrow phases (by one workgroup of a kernel of its own, 4.8 us of
     // a step: 4096 piles of 64 spheres 76.9 -> 74.1 us; 512 of 40 24.8 -> 22.4).
@@ -1796,20 +1800,22 @@ size_t collide_lds_bytes(int nq, int nb, int ng, int norient, int nsub, int nsph
 
 int mlp_pack_k32_blocks(int block) { return (mlp::kPackRecords + block - 1) / block; }
 
-template <bool ART>
+template <bool ART, bool PACK>
 static hipError_t launch_collide_a(const CollideArgs &a, const PackArgs &p, int nworld, int block, size_t lds, hipStream_t s) {
   switch (block) {
-    case 64: hipLaunchKernelGGL((collide_kernel<64, ART>), dim3(p.blocks + nworld), dim3(64), lds, s, a, p); break;
-    case 128: hipLaunchKernelGGL((collide_kernel<128, ART>), dim3(p.blocks + nworld), dim3(128), lds, s, a, p); break;
-    case 256: hipLaunchKernelGGL((collide_kernel<256, ART>), dim3(p.blocks + nworld), dim3(256), lds, s, a, p); break;
+    case 64: hipLaunchKernelGGL((collide_kernel<64, ART, PACK>), dim3(p.blocks + nworld), dim3(64), lds, s, a, p); break;
+    case 128: hipLaunchKernelGGL((collide_kernel<128, ART, PACK>), dim3(p.blocks + nworld), dim3(128), lds, s, a, p); break;
+    case 256: hipLaunchKernelGGL((collide_kernel<256, ART, PACK>), dim3(p.blocks + nworld), dim3(256), lds, s, a, p); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 hipError_t launch_collide(const CollideArgs &a, const PackArgs &p, int nworld, int block, size_t lds, hipStream_t s) {
-  return a.nsub > 0 ? launch_collide_a<true>(a, p, nworld, block, lds, s)
-                    : launch_collide_a<false>(a, p, nworld, block, lds, s);
+  if (p.blocks == 0)
+    return a.nsub > 0 ? launch_collide_a<true, false>(a, p, nworld, block, lds, s)
+                      : launch_collide_a<false, false>(a, p, nworld, block, lds, s);
+  return a.nsub > 0 ? hipErrorInvalidValue : launch_collide_a<false, true>(a, p, nworld, block, lds, s);
 }
 
 // ====================================================================
