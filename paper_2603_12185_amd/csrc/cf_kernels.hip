@@ -3473,7 +3473,7 @@ static_assert(sizeof(BodyC) % sizeof(float4) == 0 && sizeof(SubTree) == 10 * siz
 // 2048 hands and 20 steps takes 430 us in the kernel, 505 us before.  Such worlds
 // hold at most kDirectSpheres in the sphere block, so it leaves out the mask code
 // (the same batch with its scores: 484 us, 494 with that code's spills).
-template <int CONDIM, int BS, bool ART, bool LC>
+template <int CONDIM, int BS, bool ART, bool LC, int SPH>
 __global__ __launch_bounds__(BS, 2) void rollout_kernel(RolloutArgs r) {
   extern __shared__ float4 lds[];
   CollideArgs ca = r.c;
@@ -3541,7 +3541,7 @@ __global__ __launch_bounds__(BS, 2) void rollout_kernel(RolloutArgs r) {
     float4 mi0 = make_float4(1.f, 1.f, 1.f, 1.f);
     if (tid < nb) mi0 = ra.bmi[(size_t)wc * nb + tid];
     __syncthreads();
-    const int found = collide_world<BS, ART, LC ? 1 : 0>(ca, wc, sq, reg, cn, cp, cap, nxt);
+    const int found = collide_world<BS, ART, SPH>(ca, wc, sq, reg, cn, cp, cap, nxt);
     const int nc = found < cap ? found : cap;
     float4 c0n = make_float4(0.f, 0.f, 0.f, 0.f), c0p = c0n;
     if (tid < nc) {
@@ -3769,26 +3769,31 @@ hipError_t launch_rollout_free(const RolloutArgs &a, size_t lds, int waves, hipS
   }
 }
 
-template <int CONDIM, bool ART>
+template <int CONDIM, bool ART, int SPH>
 static hipError_t launch_rollout_b(const RolloutArgs &a, int block, size_t lds, hipStream_t s) {
-  if (ART && block == 64 && a.const_ofs > 0) {
-    if (a.c.nsph > kDirectSpheres) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((rollout_kernel<CONDIM, 64, ART, ART>), dim3(a.nworld), dim3(64), lds, s, a);
-    return hipGetLastError();
+  if constexpr (ART && SPH == 1) {
+    if (block == 64 && a.const_ofs > 0) {
+      hipLaunchKernelGGL((rollout_kernel<CONDIM, 64, true, true, 1>), dim3(a.nworld), dim3(64), lds, s, a);
+      return hipGetLastError();
+    }
   }
+  if (a.const_ofs > 0) return hipErrorInvalidValue;
   switch (block) {
-    case 64: hipLaunchKernelGGL((rollout_kernel<CONDIM, 64, ART, false>), dim3(a.nworld), dim3(64), lds, s, a); break;
-    case 128: hipLaunchKernelGGL((rollout_kernel<CONDIM, 128, ART, false>), dim3(a.nworld), dim3(128), lds, s, a); break;
-    case 256: hipLaunchKernelGGL((rollout_kernel<CONDIM, 256, ART, false>), dim3(a.nworld), dim3(256), lds, s, a); break;
+    case 64: hipLaunchKernelGGL((rollout_kernel<CONDIM, 64, ART, false, SPH>), dim3(a.nworld), dim3(64), lds, s, a); break;
+    case 128: hipLaunchKernelGGL((rollout_kernel<CONDIM, 128, ART, false, SPH>), dim3(a.nworld), dim3(128), lds, s, a); break;
+    case 256: hipLaunchKernelGGL((rollout_kernel<CONDIM, 256, ART, false, SPH>), dim3(a.nworld), dim3(256), lds, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
+// Articulated models hold one way of testing the sphere block: both spill more
+// (8 steps of 2048 hands at 128 threads 475 us with both, 453 with one).
 template <int CONDIM>
 static hipError_t launch_rollout_c(const RolloutArgs &a, int block, size_t lds, hipStream_t s) {
-  return a.s.nsub > 0 ? launch_rollout_b<CONDIM, true>(a, block, lds, s)
-                      : launch_rollout_b<CONDIM, false>(a, block, lds, s);
+  if (a.s.nsub == 0) return launch_rollout_b<CONDIM, false, 0>(a, block, lds, s);
+  return a.c.nsph <= kDirectSpheres ? launch_rollout_b<CONDIM, true, 1>(a, block, lds, s)
+                                    : launch_rollout_b<CONDIM, true, 2>(a, block, lds, s);
 }
 
 hipError_t launch_rollout(const RolloutArgs &a, int block, size_t lds, hipStream_t s) {
