@@ -1340,7 +1340,8 @@ __device__ __attribute__((always_inline)) inline bool sphere_masks_mfma(const fl
 // prefetch of geoms threadIdx.x and threadIdx.x + BS (each valid where below
 // ng).  Ends with a workgroup barrier.
 // SPH: the ways of testing the sphere block that the kernel holds (0: both, by
-// the block's size; 1: slot by slot; 2: masks).
+// the block's size; 1: slot by slot; 2: masks; 3: masks without the two-wave
+// matrix form).
 template <int BS, bool ART, int SPH = 0>
 __device__ int collide_world(const CollideArgs &a, int w, const float *sq, float4 *reg, float4 *outn,
                              float4 *outp, int cap, uint32_t nxt, const GeomIn *pre = nullptr, int tid_in = -1) {
@@ -1653,7 +1654,7 @@ __device__ int collide_world(const CollideArgs &a, int w, const float *sq, float
     __syncthreads();
     bool done = false;  // (uniform over the workgroup)
     if (BS == 64 && a.sph_mfma && S <= 64) done = sphere_masks_mfma<1>(Gs, g0, S, a.margin, rm, cand);
-    if (BS == 128 && a.sph_mfma && S > 64 && S <= 128) done = sphere_masks_mfma<2>(Gs, g0, S, a.margin, rm, cand);
+    if (BS == 128 && SPH != 3 && a.sph_mfma && S > 64 && S <= 128) done = sphere_masks_mfma<2>(Gs, g0, S, a.margin, rm, cand);
     if (done) {
       // masks written
     } else if (S <= 64) {
@@ -3769,31 +3770,40 @@ hipError_t launch_rollout_free(const RolloutArgs &a, size_t lds, int waves, hipS
   }
 }
 
-template <int CONDIM, bool ART, int SPH>
-static hipError_t launch_rollout_b(const RolloutArgs &a, int block, size_t lds, hipStream_t s) {
-  if constexpr (ART && SPH == 1) {
-    if (block == 64 && a.const_ofs > 0) {
-      hipLaunchKernelGGL((rollout_kernel<CONDIM, 64, true, true, 1>), dim3(a.nworld), dim3(64), lds, s, a);
-      return hipGetLastError();
-    }
-  }
-  if (a.const_ofs > 0) return hipErrorInvalidValue;
-  switch (block) {
-    case 64: hipLaunchKernelGGL((rollout_kernel<CONDIM, 64, ART, false, SPH>), dim3(a.nworld), dim3(64), lds, s, a); break;
-    case 128: hipLaunchKernelGGL((rollout_kernel<CONDIM, 128, ART, false, SPH>), dim3(a.nworld), dim3(128), lds, s, a); break;
-    case 256: hipLaunchKernelGGL((rollout_kernel<CONDIM, 256, ART, false, SPH>), dim3(a.nworld), dim3(256), lds, s, a); break;
-    default: return hipErrorInvalidValue;
-  }
+template <int CONDIM, int BS, bool ART, bool LC, int SPH>
+static hipError_t launch_rollout_k(const RolloutArgs &a, size_t lds, hipStream_t s) {
+  hipLaunchKernelGGL((rollout_kernel<CONDIM, BS, ART, LC, SPH>), dim3(a.nworld), dim3(BS), lds, s, a);
   return hipGetLastError();
 }
 
-// Articulated models hold one way of testing the sphere block: both spill more
-// (8 steps of 2048 hands at 128 threads 475 us with both, 453 with one).
+template <int CONDIM, bool ART>
+static hipError_t launch_rollout_b(const RolloutArgs &a, int block, size_t lds, hipStream_t s) {
+  const int S = a.c.nsph;
+  if (ART && block == 64 && a.const_ofs > 0)
+    return S > kDirectSpheres ? hipErrorInvalidValue : launch_rollout_k<CONDIM, 64, ART, ART, ART ? 1 : 0>(a, lds, s);
+  // Articulated models at 128 threads hold one way of testing the sphere block,
+  // and the two-wave matrix form only for blocks large enough for it: with all
+  // of them 86 registers spill, 69 with masks and 39 without (8 steps of 2048
+  // hands 475 us, 453 with one way; of 1000 pendulums over 50 spheres 204 with
+  // both masks, 184 with one).  At 64 and 256 threads one way gains nothing (50
+  // spheres 179 us with all, 184 with one).
+  if (ART && block == 128) {
+    if (S <= kDirectSpheres) return launch_rollout_k<CONDIM, 128, ART, false, ART ? 1 : 0>(a, lds, s);
+    return S <= 64 ? launch_rollout_k<CONDIM, 128, ART, false, ART ? 3 : 0>(a, lds, s)
+                   : launch_rollout_k<CONDIM, 128, ART, false, ART ? 2 : 0>(a, lds, s);
+  }
+  switch (block) {
+    case 64: return launch_rollout_k<CONDIM, 64, ART, false, 0>(a, lds, s);
+    case 128: return launch_rollout_k<CONDIM, 128, false, false, 0>(a, lds, s);
+    case 256: return launch_rollout_k<CONDIM, 256, ART, false, 0>(a, lds, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 template <int CONDIM>
 static hipError_t launch_rollout_c(const RolloutArgs &a, int block, size_t lds, hipStream_t s) {
-  if (a.s.nsub == 0) return launch_rollout_b<CONDIM, false, 0>(a, block, lds, s);
-  return a.c.nsph <= kDirectSpheres ? launch_rollout_b<CONDIM, true, 1>(a, block, lds, s)
-                                    : launch_rollout_b<CONDIM, true, 2>(a, block, lds, s);
+  return a.s.nsub > 0 ? launch_rollout_b<CONDIM, true>(a, block, lds, s)
+                      : launch_rollout_b<CONDIM, false>(a, block, lds, s);
 }
 
 hipError_t launch_rollout(const RolloutArgs &a, int block, size_t lds, hipStream_t s) {
