@@ -762,8 +762,11 @@ static cf_status adjoint_supported(const cf_model *m) {
 // a single step while the batch is one wave per SIMD and a world's contacts
 // are few: microseconds against the two kernels, 24 spheres x 256 worlds 16 / 19,
 // x 2048 32 / 23; 40 spheres x 256 23 / 22; 64 spheres 32 / 24 (their contacts
-// fill four waves at once); 16 steps of 256 worlds, per step, 16 spheres 9.2 / 20,
-// 64 spheres 27 / 28.
+// fill four waves at once).  A trajectory's step, against the two kernels and two
+// adds: 16 spheres x 256 / 1024 / 2048 / 4096 worlds 9.3 / 17, 9.8 / 18, 19.4 /
+// 24.5, 38 / 41; 32 spheres 16 / 24, 17 / 27, 32.5 / 35, 60 / 59; 64 spheres
+// 27 / 28, 29 / 42, 57 / 70, 113 / 126: no batch where the kernels win by more
+// than 2 %.
 static bool adjoint_free(const cf_model *m, int T) {
   if (m->lds_adjoint_free == 0 || m->d_act || m->mlp) return false;
   return T > 1 || (m->nb <= 32 && m->nw <= 4 * m->ncu);
@@ -935,7 +938,7 @@ cf_status cf_rollout(cf_model *m, void *stream, int32_t T, const float *q0, cons
       // contacts (a step of 256 pushers, five bodies: 4.3 us, 5.0 without;
       // 1500: 5.4, 6.2; of 1024 piles of 8 spheres: 5.1, 6.2; of 64 spheres at
       // condim 6: 15.8, 16.0); else the other one, sized for three resident
-      // waves per SIMD (twelve worlds per CU, next to no register spills)
+      // waves per SIMD (twelve worlds per CU, at most 17 spilled registers)
       // while the batch fits the device at that occupancy, else for four.
       const size_t held = cf::rollout_held_lds_bytes(m->nq, m->nb, m->ng, m->norient, m->nsph, m->ncon_max);
       const int waves = m->nw <= 4 * m->ncu ? 1 : m->nw <= 8 * m->ncu ? 2 : m->nw <= 12 * m->ncu ? 3 : 4;

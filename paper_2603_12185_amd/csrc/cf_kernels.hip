@@ -1116,13 +1116,6 @@ __device__ inline GeomIn geom_in(const CollideArgs &a, int w, int g) {
   return x;
 }
 
-// Hit masks of a sphere block of S <= 64 NWD spheres (rows of NWD words in rm,
-// zero on entry).  The lane of sphere i tests its partners j = i + d mod S,
-// d = 1 ... S/2 (d = S/2 once per pair), branch-free, collecting the hit bits in
-// NWD registers; the bits above i are ORed into row i and each bit j below i (a
-// pair reached by wrapping round) into row j at bit i (integer OR: the order of
-// the atomics does not matter).  A pair is a hit when |c_j - c_i|^2 <
-// (r_i + r_j + margin)^2 in float32, the same value from either end.
 // Contact test of a sphere pair from its LDS records (centre, radius):
 // |c_j - c_i|^2 < (r_i + r_j + margin)^2 in float32 with a fixed operation
 // order, so every path that decides a pair gets the same answer from either end.
@@ -1151,11 +1144,15 @@ __device__ inline void sphere_pair_record(float4 A, float4 B, uint32_t sl, float
   cp = make_float4(fmaf(k, nx, A.x), fmaf(k, ny, A.y), fmaf(k, nz, A.z), __uint_as_float(sl));
 }
 
-// Sphere blocks of up to this many spheres test their pairs slot by slot: a step
-// of 4096 piles of 16 / 32 / 40 / 45 spheres takes 12.2 / 16.6 / 18.7 / 21.7 us so,
-// 13.5 / 18.1 / 20.2 / 21.4 us through masks.
 static_assert(kDirectSpheres * (kDirectSpheres - 1) / 2 <= kCandCap, "every pair fits the candidate list");
 
+// Hit masks of a sphere block of S <= 64 NWD spheres (rows of NWD words in rm,
+// zero on entry).  The lane of sphere i tests its partners j = i + d mod S,
+// d = 1 ... S/2 (d = S/2 once per pair), branch-free, collecting the hit bits in
+// NWD registers; the bits above i are ORed into row i and each bit j below i (a
+// pair reached by wrapping round) into row j at bit i (integer OR: the order of
+// the atomics does not matter).  A pair is a hit when |c_j - c_i|^2 <
+// (r_i + r_j + margin)^2 in float32, the same value from either end.
 template <int BS, int NWD>
 __device__ inline void sphere_masks(const float4 *Gs, const int *gbd, int g0, int S, float margin,
                                     unsigned long long *rm) {
@@ -2526,10 +2523,9 @@ __device__ void resolve_world(const ResolveArgs &a, int w, float *sq, float *sv,
 #pragma unroll
       for (int tile = 0; tile < 4; ++tile) {
         const int row = wave * 64 + tile * 16 + cc;
-        mlp::Tile T;
-        mlp::forward_tile(lnet, [&](int t) { return lfeat[row * mlp::NIN + 4 * q + t]; }, T);
+        const mlp::f32x4 y = mlp::forward_tile(lnet, [&](int t) { return lfeat[row * mlp::NIN + 4 * q + t]; });
 #pragma unroll
-        for (int r = 0; r < 4; ++r) lout[row * mlp::NOUT + 4 * q + r] = T.y[r];
+        for (int r = 0; r < 4; ++r) lout[row * mlp::NOUT + 4 * q + r] = y[r];
       }
       __builtin_amdgcn_wave_barrier();
     }
@@ -3585,8 +3581,10 @@ size_t rollout_free_lds_bytes(int nb, int ng, int norient, int nsph) {
 
 bool rollout_free_fits(int nq, int nb) { return nb >= 1 && nb <= 64 && nq <= kCandCap; }
 
-// WAVES: resident waves per SIMD the registers are sized for (3: no spills,
-// twelve worlds per CU; 4: sixteen, a few spills).
+// WAVES: resident waves per SIMD the registers are sized for (3: 168 of them for
+// twelve worlds per CU, 0 / 2 / 8 / 17 more spilled at condim 1 / 3 / 4 / 6; 4:
+// 128 for sixteen, 20 / 30 / 50 / 62 spilled).  Eight steps of 4096 piles of
+// 64 spheres take 239 us at condim 3, 295 at condim 6, of 3000 161 and 186.
 template <int CONDIM, int WAVES>
 __global__ __launch_bounds__(64, WAVES) void rollout_free_kernel(RolloutArgs r) {
   constexpr int BS = 64;
@@ -3661,8 +3659,8 @@ __global__ __launch_bounds__(64, WAVES) void rollout_free_kernel(RolloutArgs r) 
 // dependent work is all that bounds it, so nothing of a step waits for memory.
 // Contact records and the q row have LDS of their own, the lane's state and its
 // share of the model's constants stay in registers from step to step (WAVES = 1:
-// 512 of them, 2: 256), and the applied forces of the next step are loaded
-// during this one.  32 steps of 256 pushers: 138 us, 159 with rollout_free_kernel
+// 328 to 366 of the 512; 2: all 256, with 24 to 64 spilled to the stack by
+// condim), and the applied forces of the next step are loaded during this one.  32 steps of 256 pushers: 138 us, 159 with rollout_free_kernel
 // and two copies.
 size_t rollout_held_lds_bytes(int nq, int nb, int ng, int norient, int nsph, int cap) {
   return sizeof(float) * pad4(nq) + 2 * sizeof(float4) * (size_t)cap +

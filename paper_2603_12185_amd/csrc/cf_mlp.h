@@ -1,6 +1,7 @@
 // cf_mlp.h - the learned per-contact impedance network on MFMA (bf16 inputs,
-// float32 accumulation): parameter layout and the per-wave forward pass shared
-// by the training kernels and the resolution kernel.
+// float32 accumulation): parameter layout, shared with training and batch
+// inference (cf_mlp.hip), and the per-wave forward passes of the resolution
+// kernels.
 //
 // Network (per contact): 7 features (phi, v_n, u_1, u_2, m_eff, mu_t, h),
 // normalised x = (f - mean) / std; z1 = W1^T x + b1, a1 = silu(z1) (64);
@@ -40,15 +41,11 @@ __device__ inline short to_bf16(float x) {
   return (short)(u >> 16);
 }
 
-// SiLU and its derivative with the hardware exponential and reciprocal
+// SiLU with the hardware exponential and reciprocal
 // (v_exp_f32, v_rcp_f32: about 1 ulp each, far below the bf16 rounding of the
 // activations); a large negative z gives exp = inf, rcp = 0, silu = -0.
 __device__ inline float sigmoid(float z) { return __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
 __device__ inline float silu(float z) { return z * sigmoid(z); }
-__device__ inline float dsilu(float z) {
-  const float s = sigmoid(z);
-  return s * (1.0f + z * (1.0f - s));
-}
 
 __device__ inline f32x4 mfma(bf16x4 a, bf16x4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
@@ -92,36 +89,29 @@ __device__ inline void stage_weights(const float *p, Weights *W) {
 
 __device__ inline bf16x4 lds4(const short *s) { return *reinterpret_cast<const bf16x4 *>(s); }
 
-// Activations of one tile of 16 contacts, kept for the backward pass.
-struct Tile {
-  f32x4 z1[4], z2[4];  // pre-activations, block m: rows 16 m + 4 (l / 16) + r, column l % 16
-  f32x4 y;             // outputs: rows 4 (l / 16) + r, column l % 16
-  bf16x4 x;            // input operand: x[contact l % 16][4 (l / 16) + t]
-};
-
 // Forward pass of one wave over 16 contacts.  `f4(t)` returns raw feature
-// 4 (l / 16) + t of the lane's contact l % 16 (features >= NFEAT are ignored).
+// 4 (l / 16) + t of the lane's contact l % 16 (features >= NFEAT are ignored);
+// the result holds outputs 4 (l / 16) + r of that contact.
 template <class F>
-__device__ inline void forward_tile(const Weights *W, F f4, Tile &T) {
+__device__ inline f32x4 forward_tile(const Weights *W, F f4) {
   const int l = threadIdx.x & 63, q = l >> 4, c = l & 15;
-  (void)c;
+  bf16x4 x;
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     const int k = 4 * q + t;
     const float v = k < NFEAT ? (f4(t) - W->mean[k]) * W->istd[k] : 0.f;
-    T.x[t] = to_bf16(v);
+    x[t] = to_bf16(v);
   }
   bf16x4 a1[4];
 #pragma unroll
   for (int m = 0; m < 4; ++m) {
     f32x4 z = {0.f, 0.f, 0.f, 0.f};
-    z = mfma(lds4(W->w1t + (16 * m + c) * 16 + 4 * q), T.x, z);
+    z = mfma(lds4(W->w1t + (16 * m + c) * 16 + 4 * q), x, z);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       z[r] += W->b1[16 * m + 4 * q + r];
       a1[m][r] = to_bf16(silu(z[r]));
     }
-    T.z1[m] = z;
   }
   bf16x4 a2[4];
 #pragma unroll
@@ -134,14 +124,13 @@ __device__ inline void forward_tile(const Weights *W, F f4, Tile &T) {
       z[r] += W->b2[16 * m2 + 4 * q + r];
       a2[m2][r] = to_bf16(silu(z[r]));
     }
-    T.z2[m2] = z;
   }
   f32x4 y = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int m = 0; m < 4; ++m) y = mfma(lds4(W->w3t + c * NH + 16 * m + 4 * q), a2[m], y);
 #pragma unroll
   for (int r = 0; r < 4; ++r) y[r] += W->b3[4 * q + r];
-  T.y = y;
+  return y;
 }
 
 // ---- inference inside the resolution: v_mfma_f32_16x16x32_bf16 (K = 32)
