@@ -47,6 +47,7 @@ struct cf_model {
   cf::BodyC *d_body = nullptr;
   cf::SubTree *d_sub = nullptr;
   int norient = 0, nsub = 0, art_floats = 0, artb_floats = 0;
+  int any_large = 0;     // 1: some subtree is not small
   int ydiag_floats = 0;  // the bodies' L^-1 J^T columns (exact diagonal impedance), after the work blocks
   int block_collide = 64, block_resolve = 128, block_rollout = 256;
   size_t lds_rollout = 0;
@@ -349,6 +350,7 @@ cf_status cf_model_create(const cf_model_desc *d, cf_model **out) {
   for (cf::SubTree &st : subs) {
     st.yofs = art_floats + m->ydiag_floats;
     m->ydiag_floats += 6 * st.nb * st.nd;
+    if (!st.small) m->any_large = 1;
   }
   m->nslot = (int)slots.size();
   m->box_pairs = box_pairs;
@@ -778,6 +780,7 @@ static cf::BackwardArgs backward_args(const cf_model *m) {
   b.s.mlp = m->mlp;  // learned gains: the adjoint recomputes them from the float32 parameters
   b.gpos = m->d_gpos; b.gpos_ws = m->gpos_ws;
   b.gquat = m->d_gquat; b.gquat_ws = m->gquat_ws;
+  b.any_large = m->any_large;
   return b;
 }
 

@@ -187,6 +187,7 @@ struct BackwardArgs {
   int gpos_ws, gquat_ws;
   const float *gq_out, *gv_out; // [nw][nq], [nw][nv] adjoints of q+, v+ (null = 0)
   float *gq, *gv, *gtau;        // [nw][nq], [nw][nv], [nw][nv] (gtau may be null)
+  int any_large;                // 1: some subtree is not small
 };
 
 // Adjoint of T consecutive steps (free bodies, one wave per world): the

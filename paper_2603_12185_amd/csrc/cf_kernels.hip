@@ -4643,19 +4643,25 @@ __global__ __launch_bounds__(BS) void backward_kernel(BackwardArgs b) {
   };
 
   // ---- reverse of integration and correction, per free body and per subtree
-  // (lanes 4 si .. 4 si + 3 take subtree si: a quad for a small one, its first
-  // lane for any other)
+  // (lanes 4 si .. 4 si + 3 take a small subtree si; any other one lane, counted
+  // from the last, so that in a workgroup of two waves or more it runs beside
+  // the small ones' quads instead of in turns with them: the adjoint of 4 worlds
+  // of an arm, a slide chain and a floating base 1426 -> 1404 us)
   const float *gqo = b.gq_out ? b.gq_out + (size_t)w * nq : nullptr;
   const float *gvo = b.gv_out ? b.gv_out + (size_t)w * nv : nullptr;
-  if (ART)
-  for (int t = tid; t < 4 * a.nsub; t += BS) {
-    const SubTree S = a.sub[t >> 2];
-    if (S.small)
-      small_rev_correct(S, t & 3, RR.bC, RR.bO, RR.bAx, RR.art + S.lofs, artb + S.bofs, gqo, gvo, bFb, bTb, bQb, acc,
-                        nb, P.h);
-    else if ((t & 3) == 0)
-      art_rev_correct(S, a.body, RR.bC, RR.bO, RR.bAx, RR.accF, RR.accT, RR.art + S.lofs, artb + S.bofs, sq0, sv, gqo,
-                      gvo, bFb, bTb, bQb, acc, nb, P.h);
+  if (ART) {
+    for (int t = tid; t < 4 * a.nsub; t += BS) {
+      const SubTree S = a.sub[t >> 2];
+      if (S.small)
+        small_rev_correct(S, t & 3, RR.bC, RR.bO, RR.bAx, RR.art + S.lofs, artb + S.bofs, gqo, gvo, bFb, bTb, bQb, acc,
+                          nb, P.h);
+    }
+    for (int si = b.any_large ? BS - 1 - tid : a.nsub; si < a.nsub; si += BS) {
+      const SubTree S = a.sub[si];
+      if (!S.small)
+        art_rev_correct(S, a.body, RR.bC, RR.bO, RR.bAx, RR.accF, RR.accT, RR.art + S.lofs, artb + S.bofs, sq0, sv,
+                        gqo, gvo, bFb, bTb, bQb, acc, nb, P.h);
+    }
   }
   for (int bi = tid; bi < nb; bi += BS) {
     const BodyC bc = a.body[bi];
@@ -4720,9 +4726,6 @@ __global__ __launch_bounds__(BS) void backward_kernel(BackwardArgs b) {
       if (S.small)
         small_rev_predict(S, t & 3, RR.bC, RR.bO, RR.bAx, RR.accF, RR.accT, RR.art + S.lofs, artb + S.bofs, acc, nb,
                           vw, gqo, gvo, a.act, P);
-      else if ((t & 3) == 0)
-        art_rev_predict(S, a.body, a.bmi + (size_t)w * nb, RR.bC, RR.bO, RR.bAx, RR.art + S.lofs, artb + S.bofs, acc,
-                        nb, sq0, vw, a.act, P, sq, sv, st);
     }
     __syncthreads();
     // small subtrees: thirty-two lanes each, a quad (one lane per body) for
@@ -4746,6 +4749,12 @@ __global__ __launch_bounds__(BS) void backward_kernel(BackwardArgs b) {
           sv[C.d0 + j] = R.thdb[j] + d;
         }
       }
+    }
+    for (int si = b.any_large ? BS - 1 - tid : a.nsub; si < a.nsub; si += BS) {
+      const SubTree S = a.sub[si];
+      if (!S.small)
+        art_rev_predict(S, a.body, a.bmi + (size_t)w * nb, RR.bC, RR.bO, RR.bAx, RR.art + S.lofs, artb + S.bofs, acc,
+                        nb, sq0, vw, a.act, P, sq, sv, st);
     }
   }
   for (int bi = tid; bi < nb; bi += BS) {
